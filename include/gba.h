@@ -199,7 +199,10 @@ gba_status gba_fused_workspace_size(const gba_fused_desc *desc, size_t *bytes);
  * computation, no GPU access): *tile is the tile id (see gba_tile_info), or
  * -1 for the general path and for an empty output.  The library's choice
  * depends on the shape, the layouts, the accumulation and the prologue (see
- * gba_select_tile); a requested tile_id that fits is kept.
+ * gba_select_tile); a requested tile_id that fits is kept.  When the library
+ * chooses, a request of few rows or few outputs over a long reduction may run
+ * on the few-row kernel instead, which has no tile id: the answer is then the
+ * tile it replaces.
  *
  * Errors: as gba_fused_gemm's validation; GBA_EINVAL also for tile == NULL.
  */

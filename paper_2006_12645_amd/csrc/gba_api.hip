@@ -410,11 +410,71 @@ int64_t auto_splits(int64_t M, int64_t N, int64_t ktot)
     return tiles <= 32 ? ceil_div(128, tiles) : 1;
 }
 
+// The few-row kernel's launch: row and column blocks of 16 per workgroup and
+// waves that split the reduction (tm == 0: another kernel runs).
+struct ThinCfg {
+    int tm, tn, waves;
+};
+
+// Largest leading dimension the few-row kernel addresses with 32-bit offsets.
+constexpr int64_t THIN_MAX_LD = int64_t(1) << 23;
+
+// Which requests (fp32 accumulation) the few-row kernel takes, and its
+// blocks.  Each of its workgroups streams its own panels of A and B with all
+// their reads in flight, which wins where one round of workgroups (256)
+// covers the output: the smallest blocks that do that, of 16x16, 16x32 and
+// 32x32 with column-major B, 16x32, 16x64 and 32x64 with row-major B (a
+// row-major B needs 64 bytes of each row to fill its loads).
+//   * fewer than 32 rows, where no tile fits: always (up to 16 rows the
+//     smallest blocks, else the largest, when none covers it in one round).
+//     1-16 x 4096 x 1024 RC 10.7 -> 4.1 us, 1-16 x 1024 x 4096 RC 34.6 ->
+//     5.9, RR 72 -> 7.4, CC 124 -> 6.6, 4 x 8192 x 8192 RC 96 -> 22 (6.1
+//     TB/s), RR 155 -> 29.
+//   * from 32 rows on against the tiles, warm / operands from HBM: RC 32 x
+//     1024 x 4096 8.97 / 12.3 -> 6.1 / 8.2, 128 x 512 x 4096 9.1 / 9.6 ->
+//     6.5 / 6.8, RR 64 x 1024 x 4096 11.6 / 25.4 -> 8.2 / 16, 64 x 8192^2
+//     39 / 54 -> 34 / 44, 256 x 256 x 4096 RC 9.3 / 9.6 -> 6.6 / 6.8, CC 48 x
+//     2048^2 7.8 / 11.9 -> 6.1 / 8.7.  The tiles' start-up is shorter: RC
+//     256 x 256 x 1024 4.6 / 5.3 -> 4.2 / 4.6 but 200 x 264 x 648 4.1 / 4.7
+//     against 4.4 / 4.8, so the smallest blocks from K = 768; RC 96 x 1000^2
+//     on 16x32 blocks 4.6 / 5.4 against 4.9 / 5.7 and CR 48 x 1000^2 5.8 /
+//     7.5 against 6.8 / 9.7, so the larger blocks, and any with a
+//     column-major A (read element-wise), from K = 1536.
+ThinCfg thin_cfg(const gba_fused_desc &d, bool tile_fits_fast)
+{
+    const ThinCfg none = {0, 0, 0};
+    if (d.accum != GBA_ACC_F32) return none;
+    if (d.lda >= THIN_MAX_LD || d.ldb >= THIN_MAX_LD) return none;
+    if (has_second(d) && (d.ldp >= THIN_MAX_LD || d.ldq >= THIN_MAX_LD)) return none;
+    const bool colB = d.layoutB == GBA_COL_MAJOR;
+    const int64_t ktot = d.K + (has_second(d) ? d.K2 : 0);
+    static const ThinCfg blocks[2][3] = {{{1, 2, 0}, {1, 4, 0}, {2, 4, 0}}, {{1, 1, 0}, {1, 2, 0}, {2, 2, 0}}};
+    auto groups = [&](const ThinCfg &c) { return ceil_div(d.M, 16 * c.tm) * ceil_div(d.N, 16 * c.tn); };
+    auto fits = [&](const ThinCfg &c) { return colB || d.N >= 16 * c.tn; };
+    int pick = -1;
+    for (int b = 0; b < 3 && pick < 0; ++b)
+        if (fits(blocks[colB][b]) && groups(blocks[colB][b]) <= 256) pick = b;
+    if (tile_fits_fast) {
+        if (pick < 0 || ktot < (pick > 0 || d.layoutA == GBA_COL_MAJOR ? 1536 : 768)) return none;
+    } else if (pick < 0) {
+        if (d.M >= 32 || !fits(blocks[colB][2])) return none;
+        pick = d.M <= 16 ? 0 : 2;
+    }
+    ThinCfg c = blocks[colB][pick];
+    // A wave takes at least one 64-deep slab; 16 waves pay from four each
+    // while one round covers the output (512 workgroups, 8192^2: 8 waves
+    // 22 us, 16 waves 26).
+    const int64_t slabs = ceil_div(d.K, 64) + (has_second(d) ? ceil_div(d.K2, 64) : 0);
+    c.waves = slabs < 8 ? 4 : slabs >= 64 && groups(c) <= 256 && c.tm + c.tn <= 3 ? 16 : 8;
+    return c;
+}
+
 // How a valid request runs: the tile (or the general path), the output tile
 // grid, and the split of each tile's reduction across workgroups with the
 // workspace it needs.
 struct Plan {
     int tile;          // -1: general path
+    ThinCfg thin;      // tm != 0: the few-row kernel runs instead of either
     TileCfg cfg;
     int64_t tiles_m, tiles_n;
     int64_t splits, split_steps;
@@ -428,6 +488,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     const bool two = has_second(d);
     const int64_t ktot = d.K + (two ? d.K2 : 0);
     Plan pl;
+    pl.thin = ThinCfg{0, 0, 0};
     // A requested tile that is larger than the problem is replaced by the
     // library's choice; problems smaller than every tile take the general path.
     const bool tile_ok = d.tile_id >= 0 && tile_fits(d.tile_id, d.M, d.N) &&
@@ -439,12 +500,19 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
                       : (auto_s > 1 ? AUTO_SPLIT_TILE : select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB,
                                                                             d.prologue == GBA_PRO_RELU));
     if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = -1;
+    // (a request for a split that the tile can make is kept)
+    if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2)) pl.thin = thin_cfg(d, pl.tile >= 0);
     pl.cfg = pl.tile >= 0 ? TILES[pl.tile] : GENERIC_TILE;
     pl.tiles_m = ceil_div(d.M, pl.cfg.bm);
     pl.tiles_n = ceil_div(d.N, pl.cfg.bn);
     pl.splits = 1;
     pl.split_steps = 0;
     pl.ws_bytes = 0;
+    if (pl.thin.tm) {
+        pl.tiles_m = ceil_div(d.M, 16 * pl.thin.tm);
+        pl.tiles_n = ceil_div(d.N, 16 * pl.thin.tn);
+        return pl;
+    }
     if (may_split && pl.tile >= 0 && tile_splits(pl.cfg) && fp32 && d.split_k != 1) {
         const int64_t tiles = pl.tiles_m * pl.tiles_n;
         const int64_t nk = ceil_div(d.K, 64) + (two ? ceil_div(d.K2, 64) : 0);
@@ -508,6 +576,8 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
     if (pl.tiles_m * pl.tiles_n > INT_MAX) return GBA_EUNSUPPORTED;
     a.tiles_m = (int)pl.tiles_m;
     a.tiles_n = (int)pl.tiles_n;
+    a.pro = d.prologue == GBA_PRO_RELU;
+    a.waves = pl.thin.waves;
     a.splits = (int)pl.splits;
     a.split_steps = (int)pl.split_steps;
     a.counters = pl.splits > 1 ? static_cast<unsigned *>(d.workspace) : nullptr;
@@ -515,6 +585,8 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
                                                       counter_bytes(pl.tiles_m * pl.tiles_n))
                          : nullptr;
 
+    if (pl.thin.tm)
+        return thin_launcher(d.layoutA, d.layoutB, pl.thin.tm, pl.thin.tn)(a, stream) == hipSuccess ? GBA_OK : GBA_EHIP;
     const LayoutTable &tab = table_for(d.layoutA, d.layoutB, d.prologue == GBA_PRO_RELU, two);
     const int acc16 = d.accum == GBA_ACC_F16;
     LaunchFn fn = !fast ? tab.generic[acc16] : (pl.splits > 1 ? tab.split[tile] : tab.fast[tile][acc16]);

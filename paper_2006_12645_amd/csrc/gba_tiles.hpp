@@ -14,6 +14,7 @@
 #include "gba_kernel.hpp"
 #include "gba_kernel16.hpp"
 #include "gba_kernel_generic.hpp"
+#include "gba_kernel_thin.hpp"
 
 namespace gba {
 
@@ -159,6 +160,21 @@ hipError_t launch_generic(const GemmArgs &a, hipStream_t s)
                        grid, block, 0, s, a);
     return hipGetLastError();
 }
+
+// The few-row kernel, for one layout pair (the prologue and the second
+// product are run-time options there): thin_launcher(LA, LB, TM, TN), TM in
+// {1, 2} row blocks of 16 and TN column blocks of 16 (1 or 2 with
+// column-major B, 2 or 4 with row-major B).
+template <int LA, int LB, int TM, int TN>
+hipError_t launch_thin(const GemmArgs &a, hipStream_t s)
+{
+    dim3 grid((unsigned)(a.tiles_m * a.tiles_n)), block(64 * a.waves);
+    clear_last_error();
+    hipLaunchKernelGGL((gemm_bias_act_thin<LA, LB, TM, TN>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+LaunchFn thin_launcher(int la, int lb, int tm, int tn);
 
 // Host-side launch table of one layout pair (LA, LB) and variant: PRO = ReLU
 // prologue on the left operands, DUAL = a second product.  Each
