@@ -22,6 +22,8 @@ ARCH = "gfx950"
 
 # (source, extra defines, object name)
 UNITS = [("gba_api.hip", [], "gba_api.o"), ("gba_thin_unit.hip", [], "gba_thin.o")] + [
+    ("gba_ragged_unit.hip", [f"-DGBA_LA={la}", f"-DGBA_LB={lb}"], f"gba_ragged_{'RC'[la]}{'RC'[lb]}.o")
+    for la in (0, 1) for lb in (0, 1)] + [
     ("gba_gemm_unit.hip",
      [f"-DGBA_LA={la}", f"-DGBA_LB={lb}", f"-DGBA_PRO={pro}", f"-DGBA_DUAL={dual}"],
      f"gba_gemm_{'RC'[la]}{'RC'[lb]}_p{pro}d{dual}.o")

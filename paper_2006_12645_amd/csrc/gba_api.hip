@@ -383,6 +383,13 @@ const LayoutTable &variant_table(bool pro, bool dual)
     return dual ? layout_table<LA, LB, false, true>() : layout_table<LA, LB, false, false>();
 }
 
+LaunchFn ragged_launcher(int la, int lb, int acc16, int tile)
+{
+    if (la == GBA_ROW_MAJOR)
+        return lb == GBA_ROW_MAJOR ? ragged_entry<ROW, ROW>(acc16, tile) : ragged_entry<ROW, COL>(acc16, tile);
+    return lb == GBA_ROW_MAJOR ? ragged_entry<COL, ROW>(acc16, tile) : ragged_entry<COL, COL>(acc16, tile);
+}
+
 const LayoutTable &table_for(int la, int lb, bool pro, bool dual)
 {
     if (la == GBA_ROW_MAJOR)
@@ -440,7 +447,10 @@ constexpr int64_t THIN_MAX_LD = int64_t(1) << 23;
 //     on 16x32 blocks 4.6 / 5.4 against 4.9 / 5.7 and CR 48 x 1000^2 5.8 /
 //     7.5 against 6.8 / 9.7, so the larger blocks, and any with a
 //     column-major A (read element-wise), from K = 1536.
-ThinCfg thin_cfg(const gba_fused_desc &d, bool tile_fits_fast)
+//   * against the 64x64 tile of the kernel for requests outside the fast
+//     path: from K = 768 (RC 115 x 323 x 1311 9.7 -> 6.2, CR 148 x 919 x 1217
+//     10.1 -> 9.6, RR 221 x 709 x 431 6.0 against 7.6).
+ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
 {
     const ThinCfg none = {0, 0, 0};
     if (d.accum != GBA_ACC_F32) return none;
@@ -454,8 +464,8 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool tile_fits_fast)
     int pick = -1;
     for (int b = 0; b < 3 && pick < 0; ++b)
         if (fits(blocks[colB][b]) && groups(blocks[colB][b]) <= 256) pick = b;
-    if (tile_fits_fast) {
-        if (pick < 0 || ktot < (pick > 0 || d.layoutA == GBA_COL_MAJOR ? 1536 : 768)) return none;
+    if (fast || ragged) {
+        if (pick < 0 || ktot < (fast && (pick > 0 || d.layoutA == GBA_COL_MAJOR) ? 1536 : 768)) return none;
     } else if (pick < 0) {
         if (d.M >= 32 || !fits(blocks[colB][2])) return none;
         pick = d.M <= 16 ? 0 : 2;
@@ -469,12 +479,54 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool tile_fits_fast)
     return c;
 }
 
+// The block tile of the kernel for large requests outside the fast path, or
+// -1 (the general kernel: sizes below 64, and fp16 accumulation with K no
+// multiple of 32, whose 32-deep groups the shifted last step would move).
+//   * 64x64 while two per compute unit cover the output (512 of them), then
+//     128x128: RC 289 x 6103 x 1437 (480 64x64 tiles) 20.7 / 22.2 us, 755 x
+//     2797 x 577 (528) 16.4 / 13.2, 513 x 4097 x 1001 (585) 23.3 / 18.7.
+//   * 256x256 by the two's times: 15 us + 2 us a 64-deep step for a round
+//     of 256 workgroups against 7 us + 1.4 us for a round of 512 128x128
+//     ones, of which a part-filled last round costs about half: RC 3081 x
+//     3061 x 1933 (156 of 256x256, 600 of 128x128) 67 / 75 us, 4095^3 (256,
+//     1024) 139 / 190, RR 8191 x 1023 x 4095 (128, 512) 120 / 99, CC 3429 x
+//     4717 x 1417 (266, 999) 109 / 86, RC 7247 x 5889 x 177 (696, 2679) 77 /
+//     69.
+//   * the general kernel, whose workgroups fit five to a compute unit, where
+//     two to three steps cover little more than two rounds of 64x64 tiles
+//     and it copies straight (RC): 411 x 4739 x 137 (525) 7.7 us against
+//     8.6 on 128x128, 1559 x 1713 x 71 (675) 7.2 / 7.6; but 1079 x 1911 x 71
+//     (510) 6.7 -> 6.4 on 64x64.
+// Before (general kernel): RC 4095^3 350 us, RR 665, CR 1164, CC 957; 1023^3
+// 14.4 to 63.5, now 9.6 to 10.4.
+int ragged_tile(const gba_fused_desc &d)
+{
+    const bool two = has_second(d), acc16 = d.accum == GBA_ACC_F16;
+    auto k_ok = [&](int64_t K) { return K == 0 || (K >= 64 && (!acc16 || K % 32 == 0)); };
+    if (!k_ok(d.K) || (two && !k_ok(d.K2))) return -1;
+    if (d.lda >= THIN_MAX_LD || d.ldb >= THIN_MAX_LD) return -1;
+    if (two && (d.ldp >= THIN_MAX_LD || d.ldq >= THIN_MAX_LD)) return -1;
+    auto tiles = [&](int t) -> int64_t {
+        const TileCfg &c = RAGGED_TILES[t];
+        return d.M >= c.bm && d.N >= c.bn ? ceil_div(d.M, c.bm) * ceil_div(d.N, c.bn) : 0;
+    };
+    const int64_t t0 = tiles(0), t1 = tiles(1), t2 = tiles(2);
+    const double nk = ceil_div(d.K, 64) + (two ? ceil_div(d.K2, 64) : 0);
+    const double cost0 = (15 + 2 * nk) * ceil_div(t0, 256);
+    const double cost1 = (7 + 1.4 * nk) * 0.5 * (ceil_div(t1, 512) + t1 / 512.0);
+    if (d.layoutA == GBA_ROW_MAJOR && d.layoutB == GBA_COL_MAJOR && nk <= 3 && t2 > 512 && t2 <= 700) return -1;
+    if (t0 >= 136 && cost0 <= cost1) return 0;
+    if (t1 > 0 && t2 > 512) return 1;
+    return t2 > 0 ? 2 : -1;
+}
+
 // How a valid request runs: the tile (or the general path), the output tile
 // grid, and the split of each tile's reduction across workgroups with the
 // workspace it needs.
 struct Plan {
     int tile;          // -1: general path
     ThinCfg thin;      // tm != 0: the few-row kernel runs instead of either
+    int ragged;        // block tile used instead of the general path's, or -1
     TileCfg cfg;
     int64_t tiles_m, tiles_n;
     int64_t splits, split_steps;
@@ -489,6 +541,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     const int64_t ktot = d.K + (two ? d.K2 : 0);
     Plan pl;
     pl.thin = ThinCfg{0, 0, 0};
+    pl.ragged = -1;
     // A requested tile that is larger than the problem is replaced by the
     // library's choice; problems smaller than every tile take the general path.
     const bool tile_ok = d.tile_id >= 0 && tile_fits(d.tile_id, d.M, d.N) &&
@@ -500,9 +553,12 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
                       : (auto_s > 1 ? AUTO_SPLIT_TILE : select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB,
                                                                             d.prologue == GBA_PRO_RELU));
     if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = -1;
+    if (pl.tile < 0) pl.ragged = ragged_tile(d);
     // (a request for a split that the tile can make is kept)
-    if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2)) pl.thin = thin_cfg(d, pl.tile >= 0);
-    pl.cfg = pl.tile >= 0 ? TILES[pl.tile] : GENERIC_TILE;
+    if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2))
+        pl.thin = thin_cfg(d, pl.tile >= 0, pl.ragged >= 0);
+    if (pl.thin.tm) pl.ragged = -1;
+    pl.cfg = pl.tile >= 0 ? TILES[pl.tile] : pl.ragged >= 0 ? RAGGED_TILES[pl.ragged] : GENERIC_TILE;
     pl.tiles_m = ceil_div(d.M, pl.cfg.bm);
     pl.tiles_n = ceil_div(d.N, pl.cfg.bn);
     pl.splits = 1;
@@ -589,7 +645,8 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
         return thin_launcher(d.layoutA, d.layoutB, pl.thin.tm, pl.thin.tn)(a, stream) == hipSuccess ? GBA_OK : GBA_EHIP;
     const LayoutTable &tab = table_for(d.layoutA, d.layoutB, d.prologue == GBA_PRO_RELU, two);
     const int acc16 = d.accum == GBA_ACC_F16;
-    LaunchFn fn = !fast ? tab.generic[acc16] : (pl.splits > 1 ? tab.split[tile] : tab.fast[tile][acc16]);
+    LaunchFn fn = pl.ragged >= 0 ? ragged_launcher(d.layoutA, d.layoutB, acc16, pl.ragged)
+                  : !fast ? tab.generic[acc16] : (pl.splits > 1 ? tab.split[tile] : tab.fast[tile][acc16]);
     return fn(a, stream) == hipSuccess ? GBA_OK : GBA_EHIP;
 }
 

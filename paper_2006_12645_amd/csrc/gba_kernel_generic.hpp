@@ -69,6 +69,7 @@ __device__ __forceinline__ int jperm(int t, int rho)
 // mode of its HSA runtime) serves a misaligned 16-byte load or store as one
 // instruction, so these compile to single dwordx4 accesses.
 typedef _Float16 h8u __attribute__((ext_vector_type(8), aligned(2)));
+typedef _Float16 h4u __attribute__((ext_vector_type(4), aligned(2)));
 
 // Eight consecutive fp16 from p[0..7], the ones at index >= lim read as 0.
 __device__ __forceinline__ h8 load8(const _Float16 *p, int lim)

@@ -14,6 +14,7 @@
 #include "gba_kernel.hpp"
 #include "gba_kernel16.hpp"
 #include "gba_kernel_generic.hpp"
+#include "gba_kernel_ragged.hpp"
 #include "gba_kernel_thin.hpp"
 
 namespace gba {
@@ -175,6 +176,31 @@ hipError_t launch_thin(const GemmArgs &a, hipStream_t s)
 }
 
 LaunchFn thin_launcher(int la, int lb, int tm, int tn);
+
+// Block tiles of the kernel for large requests outside the fast path
+// (gba_kernel_ragged.hpp): BM, BN, WM, WN.
+#define GBA_RAGGED_LIST(X) \
+    X(0, 256, 256, 2, 4)   \
+    X(1, 128, 128, 2, 4)   \
+    X(2, 64, 64, 2, 2)
+
+constexpr int NUM_RAGGED = 3;
+
+#define GBA_RAGGED_CFG(id, BM, BN, WM, WN) TileCfg{BM, BN, WM, WN, 1, 2},
+constexpr TileCfg RAGGED_TILES[NUM_RAGGED] = {GBA_RAGGED_LIST(GBA_RAGGED_CFG)};
+#undef GBA_RAGGED_CFG
+
+template <int BM, int BN, int WM, int WN, int LA, int LB, bool ACC16>
+hipError_t launch_ragged(const GemmArgs &a, hipStream_t s)
+{
+    dim3 grid((unsigned)(a.tiles_m * a.tiles_n)), block(64 * WM * WN);
+    clear_last_error();
+    hipLaunchKernelGGL((gemm_bias_act_ragged<BM, BN, WM, WN, LA, LB, ACC16>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+template <int LA, int LB>
+LaunchFn ragged_entry(int acc16, int tile);
 
 // Host-side launch table of one layout pair (LA, LB) and variant: PRO = ReLU
 // prologue on the left operands, DUAL = a second product.  Each
