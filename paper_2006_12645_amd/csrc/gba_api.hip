@@ -355,6 +355,55 @@ int select_tile_rest(int64_t M, int64_t N, int64_t K, int accum, int small)
     return -1;  // smaller than the smallest tile: general path
 }
 
+// The deep variant (gba_tiles.hpp) the library runs a request on (fp32
+// accumulation), or -1: the smallest one that covers the output with one
+// round of at most 256 workgroups and at least as many as given below, over
+// a reduction long enough for its start-up, when the 256x256 tile does not
+// fill the chip.  55 random shapes per layout against the tiles chosen
+// before, warm / with operands from HBM (geometric means; the limits leave
+// out what lost):
+//   * half (128x64, in RR 64x128; not in CR): RC 1.21 / 1.10x, RR 1.41 /
+//     1.34, CC 1.48 / 1.41.  1024 x 1920 x 1280 RC 12.2 -> 10.1 us, RR 15.7
+//     -> 10.7, CC 15.2 -> 10.6; 480 x 2176 x 7424 RR (136 of them, but one
+//     round of 32x128) 33.3 / 35.5.
+//   * square (128x128): RC 1.18 / 1.15x, RR 1.33 / 1.33, CR 1.18 / 1.18, CC
+//     1.34 / 1.35.  2048^3 RC 23.8 -> 20.9, RR 27.3 -> 21.3, CR 29.1 ->
+//     22.1, CC 26.5 -> 20.7; 4096 x 1024 x 8192 CR 99.5 -> 76.4 (cold 126 ->
+//     83).  CR 3648 x 448 x 512 (116) 7.4 / 9.0, 2944 x 896 x 384 (161) 8.3 /
+//     8.6, so with fewer than 200 of them in CR from K = 896.
+//   * wide (256x128, in CC 128x256), long reductions over more 128x128
+//     tiles than one round: 8192 x 1024 x 4096 RC 62.5 -> 59.4 (cold 77 ->
+//     65), RR 69.0 -> 65.7 (83 -> 69), CR 75 -> 72; RC 704 x 8192 x 6656 99 ->
+//     81; RC 4944 x 896 x 2304 (140) 29.2 / 30.7 and 7168 x 896 x 1080 cold
+//     26.9 / 29.3, so in RC from 180 of them, and from K = 2048 where an
+//     operand is read straight (RC) or both are transposed (CR), else 1280.
+int deep_choice(int64_t M, int64_t N, int64_t K, int accum, int la, int lb)
+{
+    if (accum != GBA_ACC_F32) return -1;
+    const bool rc = la == GBA_ROW_MAJOR && lb == GBA_COL_MAJOR, cr = la == GBA_COL_MAJOR && lb == GBA_ROW_MAJOR;
+    auto count = [&](const TileCfg &c) -> int64_t {
+        return c.bm > 0 && M >= c.bm && N >= c.bn ? ceil_div(M, c.bm) * ceil_div(N, c.bn) : 0;
+    };
+    if (count(TILES[1]) >= 136 || (count(TILES[1]) >= 112 && count(TILES[4]) > 512)) return -1;
+    const int64_t half = count(deep_cfg(la, lb, DEEP_HALF)), square = count(deep_cfg(la, lb, DEEP_SQUARE)),
+                  wide = count(deep_cfg(la, lb, DEEP_WIDE));
+    if (half >= 144 && half <= 256 && K >= 384) return DEEP_HALF;
+    if (cr) {
+        if (square >= 104 && square <= 256 && K >= (square >= 200 ? 384 : 896)) return DEEP_SQUARE;
+    } else if (half > 256 && square > 0 && square <= 256 && K >= 384) {
+        return DEEP_SQUARE;
+    }
+    if (square > 256 && wide <= 256 && wide >= (rc ? 180 : 128) && K >= (rc || cr ? 2048 : 1280)) return DEEP_WIDE;
+    return -1;
+}
+
+// Tile id of the library's choice and, in *deep, its deep variant or -1.
+int choose_tile(int64_t M, int64_t N, int64_t K, int accum, int la, int lb, bool pro, int *deep)
+{
+    *deep = deep_choice(M, N, K, accum, la, lb);
+    return *deep >= 0 ? deep_tile(la, lb, *deep) : select_tile(M, N, K, accum, la, lb, pro);
+}
+
 // Largest leading dimension the fast path addresses with 32-bit offsets.
 constexpr int64_t FAST_MAX_LD = int64_t(1) << 21;
 
@@ -526,6 +575,7 @@ int ragged_tile(const gba_fused_desc &d)
 struct Plan {
     int tile;          // -1: general path
     ThinCfg thin;      // tm != 0: the few-row kernel runs instead of either
+    int deep;          // deep variant of `tile`, or -1
     int ragged;        // block tile used instead of the general path's, or -1
     TileCfg cfg;
     int64_t tiles_m, tiles_n;
@@ -541,7 +591,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     const int64_t ktot = d.K + (two ? d.K2 : 0);
     Plan pl;
     pl.thin = ThinCfg{0, 0, 0};
-    pl.ragged = -1;
+    pl.ragged = pl.deep = -1;
     // A requested tile that is larger than the problem is replaced by the
     // library's choice; problems smaller than every tile take the general path.
     const bool tile_ok = d.tile_id >= 0 && tile_fits(d.tile_id, d.M, d.N) &&
@@ -549,16 +599,21 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     const bool fp32 = d.accum == GBA_ACC_F32;
     int64_t auto_s = 1;
     if (may_split && d.split_k == 0 && !tile_ok && fp32) auto_s = auto_splits(d.M, d.N, ktot);
-    pl.tile = tile_ok ? d.tile_id
-                      : (auto_s > 1 ? AUTO_SPLIT_TILE : select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB,
-                                                                            d.prologue == GBA_PRO_RELU));
-    if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = -1;
+    const bool pro = d.prologue == GBA_PRO_RELU;
+    if (tile_ok) pl.tile = d.tile_id;
+    else if (auto_s > 1) pl.tile = AUTO_SPLIT_TILE;
+    else if (may_split && d.split_k >= 2)   // deep variants do not split
+        pl.tile = select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro);
+    else pl.tile = choose_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro, &pl.deep);
+    if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = pl.deep = -1;
     if (pl.tile < 0) pl.ragged = ragged_tile(d);
     // (a request for a split that the tile can make is kept)
     if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2))
         pl.thin = thin_cfg(d, pl.tile >= 0, pl.ragged >= 0);
     if (pl.thin.tm) pl.ragged = -1;
-    pl.cfg = pl.tile >= 0 ? TILES[pl.tile] : pl.ragged >= 0 ? RAGGED_TILES[pl.ragged] : GENERIC_TILE;
+    pl.cfg = pl.deep >= 0 ? deep_cfg(d.layoutA, d.layoutB, pl.deep)
+             : pl.tile >= 0 ? TILES[pl.tile]
+             : pl.ragged >= 0 ? RAGGED_TILES[pl.ragged] : GENERIC_TILE;
     pl.tiles_m = ceil_div(d.M, pl.cfg.bm);
     pl.tiles_n = ceil_div(d.N, pl.cfg.bn);
     pl.splits = 1;
@@ -569,7 +624,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
         pl.tiles_n = ceil_div(d.N, 16 * pl.thin.tn);
         return pl;
     }
-    if (may_split && pl.tile >= 0 && tile_splits(pl.cfg) && fp32 && d.split_k != 1) {
+    if (may_split && pl.tile >= 0 && pl.deep < 0 && tile_splits(pl.cfg) && fp32 && d.split_k != 1) {
         const int64_t tiles = pl.tiles_m * pl.tiles_n;
         const int64_t nk = ceil_div(d.K, 64) + (two ? ceil_div(d.K2, 64) : 0);
         int64_t want = d.split_k >= 2 ? d.split_k : auto_s;
@@ -646,6 +701,7 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
     const LayoutTable &tab = table_for(d.layoutA, d.layoutB, d.prologue == GBA_PRO_RELU, two);
     const int acc16 = d.accum == GBA_ACC_F16;
     LaunchFn fn = pl.ragged >= 0 ? ragged_launcher(d.layoutA, d.layoutB, acc16, pl.ragged)
+                  : pl.deep >= 0 ? tab.deep[pl.deep]
                   : !fast ? tab.generic[acc16] : (pl.splits > 1 ? tab.split[tile] : tab.fast[tile][acc16]);
     return fn(a, stream) == hipSuccess ? GBA_OK : GBA_EHIP;
 }
@@ -960,7 +1016,8 @@ extern "C" int gba_select_tile(gba_layout layoutA, gba_layout layoutB, int64_t M
     if (!is_layout(layoutA) || !is_layout(layoutB)) return -1;
     if (accum != GBA_ACC_F32 && accum != GBA_ACC_F16) return -1;
     if (M < 0 || N < 0 || K < 0 || M > INT_MAX || N > INT_MAX || K > INT_MAX) return -1;
-    return select_tile(M, N, K, accum, layoutA, layoutB, false);  // -1 also when the general path would run
+    int deep;
+    return choose_tile(M, N, K, accum, layoutA, layoutB, false, &deep);  // -1 also when the general path would run
 }
 
 extern "C" gba_status gba_bias_add_f16(int64_t M, int64_t N, void *C, int64_t ldc, const void *bias,

@@ -28,6 +28,9 @@ const LayoutTable &layout_table<UNIT_LA, UNIT_LB, UNIT_PRO, UNIT_DUAL>()
     static const LayoutTable t = {
         {GBA_TILE_LIST(GBA_FAST_ENTRY)},
         {GBA_TILE_LIST(GBA_SPLIT_ENTRY)},
+        {fast_deep<UNIT_LA, UNIT_LB, UNIT_PRO, UNIT_DUAL, DEEP_WIDE>(),
+         fast_deep<UNIT_LA, UNIT_LB, UNIT_PRO, UNIT_DUAL, DEEP_SQUARE>(),
+         fast_deep<UNIT_LA, UNIT_LB, UNIT_PRO, UNIT_DUAL, DEEP_HALF>()},
         {&launch_generic<UNIT_LA, UNIT_LB, false, UNIT_PRO, UNIT_DUAL>,
          &launch_generic<UNIT_LA, UNIT_LB, true, UNIT_PRO, UNIT_DUAL>},
     };

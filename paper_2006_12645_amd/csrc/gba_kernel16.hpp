@@ -59,12 +59,15 @@ __device__ __forceinline__ int perm16(int t, int rho)
 // computing waves each 64-deep step waits for their issue).  Four of them,
 // with fp16 accumulation: 32 x 4096 x 1024 on the 32x32 tile 9.2 -> 6.8 us,
 // 1024 x 1024 x 4096 on the 64x64 tile 28.2 -> 21.7 us (one or two gave
-// less).  Not with the prologue, whose left tile is staged through the
-// computing waves' registers.
+// less).  On the larger four-wave tiles (64x32 to 128x64 warp tiles, three
+// or four stages) they leave the computing waves, one to a SIMD, nothing but
+// fragment reads and MFMAs: 4096 x 1024 x 8192 CR on 128x128 99.5 us with two
+// stages and no such waves (64x128 tile), 76.4 with.  The prologue rectifies
+// the fragments there (PROF below).
 template <int WM, int WN, int SK, bool ACC16, bool PRO, bool SPLIT>
 constexpr int copy_only_waves()
 {
-    return (WM * WN < 8 && SK == 1 && !PRO && !SPLIT) ? 4 : 0;
+    return (WM * WN < 8 && SK == 1 && !SPLIT) ? 4 : 0;
 }
 
 template <int BM, int BN, int WM, int WN, int SK, int NSTG, int LA, int LB, bool ACC16, bool PRO, bool DUAL,
@@ -87,7 +90,6 @@ gemm_bias_act_fast16(GemmArgs p)
     constexpr int SUB = (BM + BN) * ROWB;          // bytes per k-group sub-stage
     constexpr int STAGE = SK * SUB;                // bytes per LDS stage
     constexpr int NS = NSTG;
-    static_assert((NS & (NS - 1)) == 0, "stage count must be a power of two");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "warp tile must be a multiple of 32x32");
     static_assert(TN % G == 0 && (TB || G >= 2), "B blocks come in groups of two or four");
     static_assert(!(ACC16 && SK > 1), "fp16 accumulation is defined for a single running sum");
@@ -139,7 +141,9 @@ gemm_bias_act_fast16(GemmArgs p)
     // 128x64 / 64x128 tiles 7-9% faster; slower with column-major A (its
     // transposing fragment reads; 1.5-2%) and on the 128x128 tile (5-15%),
     // which keep the staged tile.
-    constexpr bool PROF = PRO && LA == ROW && WM * WN == 8 && (BM * BN == 256 * 256 || BM * BN == 128 * 64);
+    // Tiles with copy-only waves have no registers to stage through.
+    constexpr bool PROF = (PRO && NPW > 0) || (PRO && LA == ROW && WM * WN == 8 &&
+                                               (BM * BN == 256 * 256 || BM * BN == 128 * 64));
     constexpr bool PROS = PRO && !PROF;            // register-staged left tile
     constexpr bool CH = !PROS && !DUAL && !SPLIT && SK == 1 && WM * WN == 8 && BM * BN != 256 * 128 &&
                         !(ACC16 && BM * BN > 128 * 128);
@@ -338,8 +342,11 @@ gemm_bias_act_fast16(GemmArgs p)
         }
     }
 
-#pragma unroll 1
-    for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
+    // One product's reduction.  With copy-only waves each kind of wave has
+    // its own instance (COPIES: the copying one), so that the accumulators
+    // are not merged with a path that has none; without them COPIES is true.
+    auto segment = [&](int seg, auto copies) {
+        constexpr bool COPIES = decltype(copies)::value;
         const _Float16 *const X = seg == 0 ? p.A : p.P;
         const _Float16 *const Y = seg == 0 ? p.B : p.Q;
         const int64_t ldx = seg == 0 ? p.lda : p.ldp;
@@ -347,7 +354,7 @@ gemm_bias_act_fast16(GemmArgs p)
         const int Kseg = seg == 0 ? p.K : p.K2;
         if (seg == 1) {
             __syncthreads();
-            if (p.sub) negate_acc();
+            if (p.sub && (NPW == 0 || !COPIES)) negate_acc();
         }
         ca.init(ldx, ctid);
         cb.init(ldy, ctid);
@@ -392,7 +399,7 @@ gemm_bias_act_fast16(GemmArgs p)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 load_a(s);
-                if (copy_wave) copy_step(s, mine + s * STAGE);
+                if (NPW ? COPIES : copy_wave) copy_step(s, mine + s * STAGE);
                 // the prologue writes step 0's left tile now; step 1's stays
                 // in registers until the first step's barrier
                 if (PROS && s == 0) relu_store_a(mine);
@@ -401,27 +408,25 @@ gemm_bias_act_fast16(GemmArgs p)
             wait_vm_lgkm0<(NS - 1) * NL>();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            if (NPW == 0 || !copy_wave) {
+            if constexpr (NPW == 0 || !COPIES) {
                 read_a(0, mine, 0, 0);
                 read_b(0, mine, 0);
             }
         }
-        if constexpr (NPW > 0) {
+        if constexpr (NPW > 0 && COPIES) {
             // Copy-only waves: the barrier of every step, as the computing
             // waves (step kt+1 landed, step kt's stage released), then the
             // copies of step kt+NS into that stage.
-            if (copy_wave) {
-                for (int kt = 0; kt < nk; ++kt) {
-                    char *cur = mine + (kt & (NS - 1)) * STAGE;
-                    __builtin_amdgcn_sched_barrier(0);
-                    wait_vm_lgkm0<VM_AT_BARRIER>();
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_sched_barrier(0);
-                    copy_step(kt + NS, cur);
-                }
-                __builtin_amdgcn_s_waitcnt(0);
-                continue;
+            for (int kt = 0; kt < nk; ++kt) {
+                char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
+                __builtin_amdgcn_sched_barrier(0);
+                wait_vm_lgkm0<VM_AT_BARRIER>();
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                copy_step(kt + NS, cur);
             }
+            __builtin_amdgcn_s_waitcnt(0);
+            return;
         }
 
         // One reduction step.  On entry LDS stage `cur` holds step kt, steps
@@ -432,8 +437,8 @@ gemm_bias_act_fast16(GemmArgs p)
         auto run_loop = [&](auto with_copies) {
         constexpr bool WC = decltype(with_copies)::value;
         for (int kt = 0; kt < nk; ++kt) {
-            char *cur = mine + (kt & (NS - 1)) * STAGE;
-            char *nxt = mine + ((kt + 1) & (NS - 1)) * STAGE;
+            char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
+            char *nxt = mine + (int)((unsigned)(kt + 1) % NS) * STAGE;
             // slice 0: half 0, first A blocks
             read_a(1, cur, 0, 1);
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
@@ -477,14 +482,22 @@ gemm_bias_act_fast16(GemmArgs p)
             sched_slice<NM, NRB, 0x020, WC ? NL : 0, false>();
         }
         };
-        if (copy_wave) run_loop(std::true_type{});
+        if constexpr (NPW > 0) run_loop(std::false_type{});
+        else if (copy_wave) run_loop(std::true_type{});
         else run_loop(std::false_type{});
 
         __builtin_amdgcn_s_waitcnt(0);
         if (seg == 1 && p.sub) negate_acc();
+    };
+    if constexpr (NPW > 0) {
+        if (copy_wave) {   // done after the copies (the epilogue has no barrier)
+#pragma unroll 1
+            for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) segment(seg, std::true_type{});
+            return;
+        }
     }
-    // the copy-only waves are done (the epilogue has no barrier)
-    if (NPW > 0 && copy_wave) return;
+#pragma unroll 1
+    for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) segment(seg, std::bool_constant<NPW == 0>{});
     if constexpr (FOLD) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)

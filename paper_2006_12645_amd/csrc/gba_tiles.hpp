@@ -72,13 +72,39 @@ typedef hipError_t (*LaunchFn)(const GemmArgs &, hipStream_t);
 // already fill the GPU with few output tiles.
 constexpr bool tile_splits(const TileCfg &c) { return c.sk == 1 && c.bm * c.bn <= 128 * 128; }
 
+// Deep variants of a tile: four computing and four copy-only waves on the
+// 16x16x32 kernel, with as many LDS stages as fit one workgroup per compute
+// unit (fp32 accumulation).  The library takes them where one round of
+// workgroups covers the output (deep_choice in gba_api.hip); they answer to
+// the id of the tile of the same shape and waves.  Sides of 128 or more are
+// needed along an M- or N-contiguous operand, and with both operands
+// M-contiguous the wide tile is wider in N (68.6 against 67.4 us on 8192 x
+// 1024 x 4096; 39.0 / 36.6 on 4096 x 2048 x 2048).
+enum { DEEP_WIDE, DEEP_SQUARE, DEEP_HALF, NUM_DEEP };
+
+constexpr TileCfg deep_cfg(int la, int lb, int deep)
+{
+    if (deep == DEEP_SQUARE) return TileCfg{128, 128, 2, 2, 1, 4};
+    if (deep == DEEP_WIDE) return la == COL && lb == COL ? TileCfg{128, 256, 2, 2, 1, 3} : TileCfg{256, 128, 2, 2, 1, 3};
+    if (la == COL && lb == ROW) return TileCfg{0, 0, 0, 0, 0, 0};   // no half tile
+    return la == ROW && lb == ROW ? TileCfg{64, 128, 2, 2, 1, 4} : TileCfg{128, 64, 2, 2, 1, 4};
+}
+
+constexpr int deep_tile(int la, int lb, int deep)
+{
+    const TileCfg c = deep_cfg(la, lb, deep);
+    return deep == DEEP_SQUARE ? 4 : deep == DEEP_WIDE ? (c.bm > c.bn ? 2 : 3) : (c.bm > c.bn ? 5 : 7);
+}
+
 // Per operand-layout pair and kernel variant: fast[tile][acc16] for the
 // aligned fast path (null for fp16 accumulation with split-K), split[tile]
 // for its reduction split across workgroups (null where tile_splits is
-// false), generic[acc16] otherwise.
+// false), deep[variant] for its deep variants (null where there is none),
+// generic[acc16] otherwise.
 struct LayoutTable {
     LaunchFn fast[NUM_TILES][2];
     LaunchFn split[NUM_TILES];
+    LaunchFn deep[NUM_DEEP];
     LaunchFn generic[2];
 };
 
@@ -101,6 +127,7 @@ constexpr bool use_fast16(int la, int lb, int bm, int bn, int wm, int wn, int sk
 {
     const bool layouts = (bm >= 128 || la == ROW) && (bn >= 128 || lb == COL);
     if (wm * wn == 8) return layouts;
+    if (bm * bn >= 128 * 64 && nstg >= 3) return layouts && !acc16 && !split;   // deep variants
     return (acc16 || !split) && !pro && sk == 1 && nstg == 4 && layouts;
 }
 
@@ -148,6 +175,15 @@ constexpr LaunchFn fast_split()
 {
     if constexpr (tile_splits(TileCfg{BM, BN, WM, WN, SK, NSTG}))
         return &launch_fast<BM, BN, WM, WN, SK, NSTG, LA, LB, false, PRO, DUAL, true>;
+    else return nullptr;
+}
+
+// Launch-table entry for a deep variant.
+template <int LA, int LB, bool PRO, bool DUAL, int DEEP>
+constexpr LaunchFn fast_deep()
+{
+    constexpr TileCfg c = deep_cfg(LA, LB, DEEP);
+    if constexpr (c.bm > 0) return &launch_fast<c.bm, c.bn, c.wm, c.wn, c.sk, c.nstg, LA, LB, false, PRO, DUAL>;
     else return nullptr;
 }
 
