@@ -186,14 +186,14 @@ int select_tile(int64_t M, int64_t N, int64_t K, int accum, int la, int lb, bool
         } else if (la == lb && !pro) {
             // RR and CC: the four-stage tile with its long side along the
             // operand's contiguous direction (32x128 in RR, 128x32 in CC)
-            // up to one round of 256 workgroups, where it does not fit the
-            // 32x64 tile on memory-bound thin shapes, else the 8-wave
-            // tiles below (on 36 thin shapes per layout, warm and with
-            // operands from HBM: 5.5% / 0% slower in total than the
-            // per-shape best tile in RR and 3.0% / 0.5% in CC, against
-            // 21% / 49% and 16% / 27% for the rule before)
+            // up to one workgroup per compute unit, from K = 1024 two, else
+            // the 8-wave tiles below.  With its 32x32 warp tiles (four computing waves) it
+            // takes 1088 x 1792 x 3072 RR (476 workgroups) in 31.4 us against
+            // 37.1 on the 8-wave 64x128 tile (from HBM 34.8 / 45.3), 4032 x
+            // 320 x 4544 CC (320) 37.7 / 49.2 (40.7 / 62.6); 4864 x 704 x
+            // 2112 RR (912) 43.6 / 33.0, 896 x 1472 x 576 CC (322) 9.0 / 7.8.
             const int tn = la == GBA_ROW_MAJOR ? 24 : 25;
-            if (tile_fits(tn, M, N) && tiles(tn) <= 256) return tn;
+            if (tile_fits(tn, M, N) && tiles(tn) <= (K >= 1024 ? 512 : 256)) return tn;
             if (ai < RIDGE_AI && (M <= 256 || N <= 256) && tile_fits(8, M, N) && tiles(8) <= 256) return 8;
         } else if (la == lb) {
             // RR and CC with the prologue, where those tiles have no
@@ -496,6 +496,9 @@ constexpr int64_t THIN_MAX_LD = int64_t(1) << 23;
 //     on 16x32 blocks 4.6 / 5.4 against 4.9 / 5.7 and CR 48 x 1000^2 5.8 /
 //     7.5 against 6.8 / 9.7, so the larger blocks, and any with a
 //     column-major A (read element-wise), from K = 1536.
+//     With column-major B the tiles keep what needs 32x32 blocks (RC 128 x
+//     2048^2 6.6 / 8.5 against 7.7 / 9.5, CC 320 x 704 x 2880 13.2 / 13.1
+//     against 15.2 / 15.0).
 //   * against the 64x64 tile of the kernel for requests outside the fast
 //     path: from K = 768 (RC 115 x 323 x 1311 9.7 -> 6.2, CR 148 x 919 x 1217
 //     10.1 -> 9.6, RR 221 x 709 x 431 6.0 against 7.6).
@@ -515,6 +518,7 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
         if (fits(blocks[colB][b]) && groups(blocks[colB][b]) <= 256) pick = b;
     if (fast || ragged) {
         if (pick < 0 || ktot < (fast && (pick > 0 || d.layoutA == GBA_COL_MAJOR) ? 1536 : 768)) return none;
+        if (fast && colB && pick == 2) return none;
     } else if (pick < 0) {
         if (d.M >= 32 || !fits(blocks[colB][2])) return none;
         pick = d.M <= 16 ? 0 : 2;

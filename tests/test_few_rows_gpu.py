@@ -58,7 +58,7 @@ def test_fewer_rows_than_any_tile(M, N, K, K2, layout):
     (32, 264, 4096, 0),     # 16 waves, whole slabs
     (256, 256, 1544, 0),    # the last of one round of 16x16 workgroups (column-major B)
     (40, 2048, 1600, 264),  # 16x32 / 16x64 blocks, both products
-    (64, 4096, 1536, 0),    # 32x32 / 32x64 blocks
+    (64, 4096, 1536, 0),    # 32x64 blocks (row-major B)
 ])
 def test_taken_from_the_tiles(M, N, K, K2, layout):
     check(M, N, K, layout, K2, second="add", prologue="relu" if K2 else None, bias="row", bias_op="add", act="relu",
