@@ -173,19 +173,19 @@ void gba_fused_desc_init(gba_fused_desc *desc);
  * block; this is the same partition across blocks): when an output has too
  * few tiles to occupy the GPU, or a long reduction, each output tile's
  * reduction steps (A.B's, then P.Q's) are divided among up to split_k
- * workgroups.  Each writes its fp32 partial tile to the workspace; the last
- * of a tile's splits to finish adds the partials in split order (the result
- * does not depend on which finishes last) and runs the epilogue.  Only the
- * summation order changes, not the tolerance; GBA_ACC_F16 never splits.
+ * workgroups.  Each writes its fp32 partial tile to the workspace; a second
+ * kernel on the same stream adds the partials in split order and runs the
+ * epilogue.  Only the summation order changes, not the tolerance;
+ * GBA_ACC_F16 never splits.
  *
  * Workspace contract (gba_fused_gemm): at least this many bytes, 256-byte
  * aligned, on the device the call runs on, and all zero when the call is
- * enqueued.  A call that splits uses it for one 32-bit counter per output
- * tile followed by the fp32 partial tiles, and leaves every byte it used
- * at zero again when it completes, so a workspace zero-filled once serves
+ * enqueued.  A call that splits uses it for the fp32 partial tiles (after a
+ * reserved 32-bit word per output tile), and leaves every byte it used at
+ * zero again when it completes, so a workspace zero-filled once serves
  * any number of calls in stream order, whatever their shapes and tiles;
- * calls that may run at the same time need separate workspaces.  With a NULL or smaller workspace the
- * call runs unsplit.  split_k >= 2 asks for that many splits (fewer when
+ * calls that may run at the same time need separate workspaces.  With a NULL
+ * or smaller workspace the call runs unsplit.  split_k >= 2 asks for that many splits (fewer when
  * the reduction has fewer 64-deep steps); 0 lets the library decide.
  *
  * Errors: as gba_fused_gemm's validation; GBA_EINVAL also for bytes ==
@@ -262,16 +262,14 @@ gba_status gba_fused_gemm(const gba_fused_desc *desc, gba_stream_t stream);
  * When the request splits its reduction across workgroups, the split's
  * workspace is the library's own static device array of
  * GBA_NOALLOC_SCRATCH_BYTES bytes (one per GPU, created with the library's
- * code object and held until the process ends); its counters are cleared by
- * a small kernel on `stream` before the split kernel.  Requests that do not
+ * code object and held until the process ends).  Requests that do not
  * split use no scratch.  The call allocates nothing (no hipMalloc, no
  * allocating library routine); its first call on a device looks up that
  * device's scratch address once, with the device current.
  *
- * Every call on one GPU shares that GPU's scratch, which keeps the last
- * call's contents: calls that may overlap on one GPU (different streams,
- * different host threads without ordering) race on it and give undefined
- * results.  Calls in one stream's order are safe.
+ * Every call on one GPU shares that GPU's scratch: calls that may overlap on
+ * one GPU (different streams, different host threads without ordering) race
+ * on it and give undefined results.  Calls in one stream's order are safe.
  *
  * Errors: as gba_fused_gemm; GBA_ESCRATCH (nothing launched) when the split
  * the request asks for (or the library chooses) needs more than

@@ -451,12 +451,18 @@ constexpr int64_t MAX_SPLITS = 64;
 
 // The library splits a reduction by itself (split_k == 0) only where that
 // was measured to win: reductions of 16384 or more over so few outputs that
-// the 64x64 tile makes at most 32 workgroups.  There the 64x64 tile with
-// about 128 workgroups in all beats every unsplit tile 1.6-2.7x
-// (64x512x32768: 30 us against 50; 128x128x65536: 35 against 94).  On
-// shorter reductions the partial-tile traffic and the device-scope release
-// of every split cost more than the extra workgroups gain.
-constexpr int AUTO_SPLIT_TILE = 6;
+// the 64x64 tile makes at most 32 workgroups, into about 128 shares of 64x64
+// tiles; run as 32x64 tiles (twice the workgroups over the same partial
+// sums), whose four-stage kernel has copy-only waves, where that kernel
+// exists (RC without the prologue), else on the 64x64 tile.  64 x 512 x 32768
+// RC: 50 us on the best unsplit tile.
+constexpr int AUTO_SPLIT_TILE = 6, AUTO_SPLIT_TILE_RC = 21;
+
+int auto_split_tile(const gba_fused_desc &d)
+{
+    const bool rc = d.layoutA == GBA_ROW_MAJOR && d.layoutB == GBA_COL_MAJOR;
+    return rc && d.prologue != GBA_PRO_RELU ? AUTO_SPLIT_TILE_RC : AUTO_SPLIT_TILE;
+}
 
 int64_t auto_splits(int64_t M, int64_t N, int64_t ktot)
 {
@@ -605,7 +611,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     if (may_split && d.split_k == 0 && !tile_ok && fp32) auto_s = auto_splits(d.M, d.N, ktot);
     const bool pro = d.prologue == GBA_PRO_RELU;
     if (tile_ok) pl.tile = d.tile_id;
-    else if (auto_s > 1) pl.tile = AUTO_SPLIT_TILE;
+    else if (auto_s > 1) pl.tile = auto_split_tile(d);
     else if (may_split && d.split_k >= 2)   // deep variants do not split
         pl.tile = select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro);
     else pl.tile = choose_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro, &pl.deep);
@@ -658,6 +664,47 @@ Plan plan_for(const gba_fused_desc &d)
     return pl;
 }
 
+// Second kernel of a reduction split across workgroups: every thread sums
+// the splits' partial sums of 4 consecutive outputs of a tile row in split
+// order, puts them back to zero (the workspace contract: a later call with
+// other tiles finds every byte zero) and runs the epilogue.  A launch of its
+// own costs about 3 us of the 39 that 64 x 512 x 32768 RC took when the last
+// split of a tile to finish summed all of them in one workgroup, after every
+// split's device-scope release had written back its XCD's cache; the kernel
+// boundary orders the partial sums instead, and the sums spread over the
+// chip (64-thread workgroups: 128 of them here).
+constexpr int REDUCE_OUTPUTS = 256;   // outputs per workgroup
+
+__global__ void __launch_bounds__(REDUCE_OUTPUTS / 4) split_reduce_kernel(GemmArgs p, int bm, int bn)
+{
+    const int per_tile = bm * bn / REDUCE_OUTPUTS;
+    const int tile_id = (int)blockIdx.x / per_tile;
+    const int e = (((int)blockIdx.x % per_tile) * (REDUCE_OUTPUTS / 4) + (int)threadIdx.x) * 4;   // output in the tile
+    int tm, tn;
+    tile_coords(tile_id, p.tiles_m * p.tiles_n, p.tiles_m, tm, tn);
+    const int m0 = tm * bm, n0 = tn * bn;
+    const int mc = m0 + bm <= p.M ? m0 : p.M - bm, nc = n0 + bn <= p.N ? n0 : p.N - bn;
+    const int i = mc + e / bn, j = nc + e % bn;
+    float *part = p.ws + (size_t)tile_id * p.splits * (bm * bn) + e;
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int k = 0; k < p.splits; ++k) {
+        const f4 v = *reinterpret_cast<const f4 *>(part + (size_t)k * (bm * bn));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] += v[c];
+    }
+    for (int k = 0; k < p.splits; ++k) *reinterpret_cast<f4 *>(part + (size_t)k * (bm * bn)) = f4{0.f, 0.f, 0.f, 0.f};
+    if (i < m0 || j < n0) return;   // a neighbouring tile's output
+    if (p.bias_kind != BIAS_NONE) {
+        const h4 b = *reinterpret_cast<const h4 *>(p.bias + j + (p.bias_kind == BIAS_FULL ? (int64_t)i * p.ldbias : 0));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] += p.bias_sign * (float)b[c];
+    }
+    activate(p.act, x);
+    *reinterpret_cast<h4 *>(p.C + (int64_t)i * p.ldc + j) =
+        h4{(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3]};
+}
+
 gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
 {
     gba_status st = validate(d);
@@ -695,7 +742,6 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
     a.waves = pl.thin.waves;
     a.splits = (int)pl.splits;
     a.split_steps = (int)pl.split_steps;
-    a.counters = pl.splits > 1 ? static_cast<unsigned *>(d.workspace) : nullptr;
     a.ws = pl.splits > 1 ? reinterpret_cast<float *>(static_cast<char *>(d.workspace) +
                                                       counter_bytes(pl.tiles_m * pl.tiles_n))
                          : nullptr;
@@ -707,7 +753,14 @@ gba_status run_fused(const gba_fused_desc &d, hipStream_t stream)
     LaunchFn fn = pl.ragged >= 0 ? ragged_launcher(d.layoutA, d.layoutB, acc16, pl.ragged)
                   : pl.deep >= 0 ? tab.deep[pl.deep]
                   : !fast ? tab.generic[acc16] : (pl.splits > 1 ? tab.split[tile] : tab.fast[tile][acc16]);
-    return fn(a, stream) == hipSuccess ? GBA_OK : GBA_EHIP;
+    if (fn(a, stream) != hipSuccess) return GBA_EHIP;
+    if (pl.splits > 1) {
+        clear_last_error();
+        const unsigned groups = (unsigned)(pl.tiles_m * pl.tiles_n * ((int64_t)pl.cfg.bm * pl.cfg.bn / REDUCE_OUTPUTS));
+        hipLaunchKernelGGL(split_reduce_kernel, dim3(groups), dim3(REDUCE_OUTPUTS / 4), 0, stream, a, pl.cfg.bm, pl.cfg.bn);
+        if (hipGetLastError() != hipSuccess) return GBA_EHIP;
+    }
+    return GBA_OK;
 }
 
 // The request of gemm_bias_act: one product, no prologue, row bias if any.
@@ -864,8 +917,7 @@ gba_status validate_pointwise(int64_t M, int64_t N, const void *C, int64_t ldc, 
 
 // ---------------------------------------------------------------------------
 // Library-held scratch of gba_fused_gemm_noalloc: the workspace of a
-// reduction split across workgroups (per-tile arrival counters, then the
-// fp32 partial tiles), for callers that cannot allocate.  One copy per GPU,
+// reduction split across workgroups (the fp32 partial tiles), for callers that cannot allocate.  One copy per GPU,
 // at its own device address, held until the process ends.  In host code
 // the array's name is only a host-side stand-in: kernels and copies get the
 // device address from hipGetSymbolAddress, taken once per device.
@@ -896,14 +948,6 @@ gba_status device_scratch(void **ptr)
     if (scratch_err[dev] != hipSuccess || scratch_ptr[dev] == nullptr) return GBA_EHIP;
     *ptr = scratch_ptr[dev];
     return GBA_OK;
-}
-
-// Sets n 32-bit words to zero: the split counters are cleared with a kernel
-// (a memset node in a captured graph is not reliable on this platform).
-__global__ void __launch_bounds__(256) zero_words_kernel(unsigned *p, int n)
-{
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < n) p[i] = 0u;
 }
 
 }  // namespace
@@ -966,14 +1010,6 @@ extern "C" gba_status gba_fused_gemm_noalloc(const gba_fused_desc *desc, gba_str
         void *ws = nullptr;
         st = device_scratch(&ws);
         if (st != GBA_OK) return st;
-        // The counters must be zero when the split kernel starts, whatever an
-        // earlier call left behind.
-        const int64_t ntiles = pl.tiles_m * pl.tiles_n;
-        hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-        clear_last_error();
-        hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)ceil_div(ntiles, 256)), dim3(256), 0, s,
-                           static_cast<unsigned *>(ws), (int)ntiles);
-        if (hipGetLastError() != hipSuccess) return GBA_EHIP;
         d.workspace = ws;
         d.workspace_bytes = NOALLOC_SCRATCH_BYTES;
     }

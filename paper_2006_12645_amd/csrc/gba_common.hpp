@@ -40,12 +40,10 @@ struct GemmArgs {
     // Reduction split across workgroups (splits > 1): workgroup b computes
     // split b % splits of output tile b / splits, i.e. reduction steps
     // [split * split_steps, (split + 1) * split_steps) of the steps of A.B
-    // followed by those of P.Q; its fp32 partial tile goes to ws and the
-    // last split of a tile to arrive (counted in counters, which start and
-    // end at zero) sums them in split order and runs the epilogue.
+    // followed by those of P.Q, and writes its fp32 partial tile to
+    // ws[tile][split], which a second kernel sums in split order.
     int splits, split_steps;
     float *ws;
-    unsigned *counters;
 };
 
 __device__ __forceinline__ h8 zero_h8()

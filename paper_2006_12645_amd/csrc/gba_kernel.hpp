@@ -380,8 +380,8 @@ __device__ __forceinline__ h8 read_frag_tr(const char *p)
 // steps, and only the sum (or difference) leaves the kernel.
 // SPLIT: each output tile's reduction is split across p.splits workgroups
 // (the grid holds p.splits workgroups per tile); every split writes its
-// fp32 partial tile to p.ws and the last one of a tile to arrive sums them
-// in split order and runs the epilogue.
+// fp32 partial tile to p.ws, and split_reduce_kernel, launched after this
+// one, sums them in split order and runs the epilogue.
 template <int BM, int BN, int WM, int WN, int SK, int NSTG, int LA, int LB, bool ACC16, bool PRO, bool DUAL,
           bool SPLIT>
 __global__ void __launch_bounds__(64 * WM * WN * SK) gemm_bias_act_fast(GemmArgs p)
@@ -667,77 +667,19 @@ __global__ void __launch_bounds__(64 * WM * WN * SK) gemm_bias_act_fast(GemmArgs
     }
 
     if constexpr (SPLIT) {
-        {
-            // Partial tile of this split to the workspace, each thread's
-            // accumulators of a 32x32 block as 16 consecutive floats (a wave
-            // writes 4 KB contiguously per block).
-            float *const part = p.ws + (size_t)tile_id * p.splits * (BM * BN);
+        // Partial tile of this split to the workspace, row by row; the
+        // reduction kernel sums the splits and runs the epilogue.
+        float *const part = p.ws + ((size_t)tile_id * p.splits + kspl) * (BM * BN);
 #pragma unroll
-            for (int t = 0; t < TN; ++t)
+        for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int s = 0; s < TM; ++s) {
-                    f4 *dst = reinterpret_cast<f4 *>(part + (size_t)kspl * (BM * BN) + ((t * TM + s) * NT + tid) * 16);
+            for (int s = 0; s < TM; ++s) {
+                f4 *dst = reinterpret_cast<f4 *>(part + (wm * WTM + 32 * s + l32) * BN + wn * WTN + 32 * t + 16 * hi);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        dst[q] = f4{acc[t][s][4 * q], acc[t][s][4 * q + 1], acc[t][s][4 * q + 2], acc[t][s][4 * q + 3]};
-                }
-            // Count this split in, releasing the workgroup's partial (all of
-            // its stores are done at the barrier) at device scope; the last
-            // split to arrive acquires every other split's partial and goes
-            // on, the others are done.  One release per workgroup and one
-            // acquire per output tile: an acquire invalidates the cached
-            // operands of every workgroup sharing the cache.
-            __syncthreads();
-            __shared__ int last_split;
-            if (tid == 0) {
-                const unsigned before = __hip_atomic_fetch_add(p.counters + tile_id, 1u, __ATOMIC_RELEASE,
-                                                               __HIP_MEMORY_SCOPE_AGENT);
-                last_split = before == (unsigned)(p.splits - 1);
-                if (last_split) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                for (int q = 0; q < 4; ++q)
+                    dst[q] = f4{acc[t][s][4 * q], acc[t][s][4 * q + 1], acc[t][s][4 * q + 2], acc[t][s][4 * q + 3]};
             }
-            __syncthreads();
-            if (!__builtin_amdgcn_readfirstlane(last_split)) return;
-            // Sum of the partials in split order (independent of arrival
-            // order, so the result is deterministic); the counter is reset
-            // for the next call.
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int s = 0; s < TM; ++s)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[t][s][e] = 0.f;
-            for (int j = 0; j < p.splits; ++j) {
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int s = 0; s < TM; ++s) {
-                        const f4 *src =
-                            reinterpret_cast<const f4 *>(part + (size_t)j * (BM * BN) + ((t * TM + s) * NT + tid) * 16);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const f4 v = src[q];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[t][s][4 * q + e] += v[e];
-                        }
-                    }
-            }
-            // The partials go back to zero like the counter: a later call
-            // with more output tiles keeps counters where this call kept
-            // partials, and the workspace contract is that every byte a
-            // call uses is zero when it completes.
-            for (int j = 0; j < p.splits; ++j) {
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int s = 0; s < TM; ++s) {
-                        f4 *dst = reinterpret_cast<f4 *>(part + (size_t)j * (BM * BN) + ((t * TM + s) * NT + tid) * 16);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) dst[q] = f4{0.f, 0.f, 0.f, 0.f};
-                    }
-            }
-            if (tid == 0)
-                __hip_atomic_store(p.counters + tile_id, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        return;
     }
 
     if constexpr (SK > 1) {

@@ -64,20 +64,20 @@ __device__ __forceinline__ int perm16(int t, int rho)
 // fragment reads and MFMAs: 4096 x 1024 x 8192 CR on 128x128 99.5 us with two
 // stages and no such waves (64x128 tile), 76.4 with.  The prologue rectifies
 // the fragments there (PROF below).
-template <int WM, int WN, int SK, bool ACC16, bool PRO, bool SPLIT>
+template <int WM, int WN, int SK>
 constexpr int copy_only_waves()
 {
-    return (WM * WN < 8 && SK == 1 && !SPLIT) ? 4 : 0;
+    return (WM * WN < 8 && SK == 1) ? 4 : 0;
 }
 
 template <int BM, int BN, int WM, int WN, int SK, int NSTG, int LA, int LB, bool ACC16, bool PRO, bool DUAL,
           bool SPLIT>
-__global__ void __launch_bounds__(64 * (WM * WN * SK + copy_only_waves<WM, WN, SK, ACC16, PRO, SPLIT>()))
+__global__ void __launch_bounds__(64 * (WM * WN * SK + copy_only_waves<WM, WN, SK>()))
 gemm_bias_act_fast16(GemmArgs p)
 {
     constexpr int NTG = 64 * WM * WN;         // threads per k-group
     constexpr int NT = NTG * SK;              // threads that compute
-    constexpr int NPW = copy_only_waves<WM, WN, SK, ACC16, PRO, SPLIT>();
+    constexpr int NPW = copy_only_waves<WM, WN, SK>();
     constexpr int BK = 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TM = WTM / 16, TN = WTN / 16;   // 16x16 blocks of the warp tile
@@ -508,50 +508,16 @@ gemm_bias_act_fast16(GemmArgs p)
     }
 
     if constexpr (SPLIT) {
-        {
-            // Partial tile of this split to the workspace, each thread's 4
-            // accumulators of a 16x16 block as one 16-byte write.
-            float *const part = p.ws + (size_t)tile_id * p.splits * (BM * BN);
+        // Partial tile of this split to the workspace, row by row (see the
+        // 32x32 kernel): 4 outputs of a row per lane and 16x16 block.
+        float *const part = p.ws + ((size_t)tile_id * p.splits + kspl) * (BM * BN);
 #pragma unroll
-            for (int t = 0; t < TN; ++t)
+        for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int s = 0; s < TM; ++s)
-                    *reinterpret_cast<f4 *>(part + (size_t)kspl * (BM * BN) + ((t * TM + s) * NT + tid) * 4) =
-                        acc[t][s];
-            __syncthreads();
-            __shared__ int last_split;
-            if (tid == 0) {
-                const unsigned before = __hip_atomic_fetch_add(p.counters + tile_id, 1u, __ATOMIC_RELEASE,
-                                                               __HIP_MEMORY_SCOPE_AGENT);
-                last_split = before == (unsigned)(p.splits - 1);
-                if (last_split) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            }
-            __syncthreads();
-            if (!__builtin_amdgcn_readfirstlane(last_split)) return;
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int s = 0; s < TM; ++s) acc[t][s] = f4{0.f, 0.f, 0.f, 0.f};
-            for (int j = 0; j < p.splits; ++j) {
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int s = 0; s < TM; ++s)
-                        acc[t][s] += *reinterpret_cast<const f4 *>(part + (size_t)j * (BM * BN) +
-                                                                   ((t * TM + s) * NT + tid) * 4);
-            }
-            // partials back to zero (see the 32x32 kernel)
-            for (int j = 0; j < p.splits; ++j) {
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int s = 0; s < TM; ++s)
-                        *reinterpret_cast<f4 *>(part + (size_t)j * (BM * BN) + ((t * TM + s) * NT + tid) * 4) =
-                            f4{0.f, 0.f, 0.f, 0.f};
-            }
-            if (tid == 0)
-                __hip_atomic_store(p.counters + tile_id, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+            for (int s = 0; s < TM; ++s)
+                *reinterpret_cast<f4 *>(part + (wm * WTM + 16 * s + l16) * BN + wn * WTN + 16 * G * (t / G) +
+                                        4 * G * g4 + 4 * (t % G)) = acc[t][s];
+        return;
     }
 
     if constexpr (SK > 1) {

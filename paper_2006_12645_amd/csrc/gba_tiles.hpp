@@ -115,8 +115,7 @@ struct LayoutTable {
 // with eight waves of one k-group, in every layout where an M- or
 // N-contiguous operand tile has 128 or more elements per row (its
 // conflict-free group permutation needs eight 16-element groups); and,
-// without prologue and unless the reduction is split across workgroups,
-// the four-stage small tiles (21-25) under the same layout condition (all
+// without prologue, the four-stage small tiles (21-25) under the same layout condition (all
 // of them in the layout where both operand tiles are reduction-contiguous,
 // 32x128 with row-major B, 128x32 with column-major A), where the 16x16x32
 // kernel adds waves that only issue copies (with fp16 accumulation its
@@ -131,7 +130,7 @@ constexpr bool use_fast16(int la, int lb, int bm, int bn, int wm, int wn, int sk
     const bool layouts = (bm >= 128 || la == ROW) && (bn >= 128 || lb == COL);
     if (wm * wn == 8) return layouts;
     if (bm * bn >= 128 * 64 && nstg >= 3) return layouts && !acc16 && !split;   // deep variants
-    return (acc16 || !split) && !pro && sk == 1 && nstg == 4 && layouts;
+    return !pro && sk == 1 && nstg == 4 && layouts;
 }
 
 // hipGetLastError reports the last failure of any runtime call on the
@@ -146,7 +145,7 @@ hipError_t launch_fast(const GemmArgs &a, hipStream_t s)
 {
     // one workgroup per output tile, times the splits of its reduction
     constexpr int NPW = use_fast16(LA, LB, BM, BN, WM, WN, SK, NSTG, ACC16, PRO, SPLIT)
-                            ? copy_only_waves<WM, WN, SK, ACC16, PRO, SPLIT>() : 0;
+                            ? copy_only_waves<WM, WN, SK>() : 0;
     dim3 grid((unsigned)(a.tiles_m * a.tiles_n * (SPLIT ? a.splits : 1))), block(64 * (WM * WN * SK + NPW));
     // The 8-wave tiles (one k-group) run on 16x16x32 MFMAs, and so do the
     // four-stage small tiles where use_fast16 allows them;
