@@ -342,11 +342,74 @@ gemm_bias_act_fast16(GemmArgs p)
         }
     }
 
-    // One product's reduction.  With copy-only waves each kind of wave has
-    // its own instance (COPIES: the copying one), so that the accumulators
-    // are not merged with a path that has none; without them COPIES is true.
-    auto segment = [&](int seg, auto copies) {
-        constexpr bool COPIES = decltype(copies)::value;
+    // The steps [s_lo, s_lo + nk) of a product that this workgroup reduces.
+    auto step_range = [&](int seg, int Kseg, int &lo_out, int &nk) {
+        const int nk_seg = (Kseg + SK * BK - 1) / (SK * BK);
+        int s_lo = 0, s_hi = nk_seg;
+        if constexpr (SPLIT) {
+            const int off = seg == 0 ? 0 : (p.K + SK * BK - 1) / (SK * BK);
+            const int lo = kspl * p.split_steps - off, hi = lo + p.split_steps;
+            s_lo = __builtin_amdgcn_readfirstlane(lo < 0 ? 0 : (lo > nk_seg ? nk_seg : lo));
+            s_hi = __builtin_amdgcn_readfirstlane(hi < 0 ? 0 : (hi > nk_seg ? nk_seg : hi));
+        }
+        lo_out = s_lo;
+        nk = s_hi - s_lo;
+    };
+
+    // Copy-only waves: the barriers of the computing waves (the first step
+    // landed, then at every step: step kt+1 landed, step kt's stage released),
+    // after each of the latter the copies of step kt+NS into that stage.  A
+    // loop of their own, so that the accumulators are not merged with a path
+    // that has none; the shared loop below stays a plain one, since as a
+    // lambda called for either kind of wave it made the 256x256 kernels
+    // without such waves spill more (CR fp32 12 registers against 6: 5176 x
+    // 4456 x 128 27.9 us against 25.3).
+    if constexpr (NPW > 0) {
+        if (copy_wave) {
+#pragma unroll 1
+            for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
+                const _Float16 *const X = seg == 0 ? p.A : p.P;
+                const _Float16 *const Y = seg == 0 ? p.B : p.Q;
+                const int64_t ldx = seg == 0 ? p.lda : p.ldp;
+                const int64_t ldy = seg == 0 ? p.ldb : p.ldq;
+                const int Kseg = seg == 0 ? p.K : p.K2;
+                int s_lo, nk;
+                step_range(seg, Kseg, s_lo, nk);
+                if (seg == 1) __syncthreads();
+                ca.init(ldx, ctid);
+                cb.init(ldy, ctid);
+                auto copy_step = [&](int s, char *stage) {
+                    const int k0 = __builtin_amdgcn_readfirstlane(((s < nk ? s : nk - 1) + s_lo) * BK);
+                    const int kleft = s < nk ? Kseg - k0 : 0;
+                    ca.dma(make_rsrc(X + (TA ? (int64_t)k0 * ldx + mc : (int64_t)mc * ldx + k0), MAX_RECORDS), stage,
+                           kleft);
+                    cb.dma(make_rsrc(Y + (TB ? (int64_t)k0 * ldy + nc : (int64_t)nc * ldy + k0), MAX_RECORDS),
+                           stage + BM * ROWB, kleft);
+                };
+                if (nk > 0) {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) copy_step(s, mine + s * STAGE);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_vm_lgkm0<(NS - 1) * NL>();
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                for (int kt = 0; kt < nk; ++kt) {
+                    char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_vm_lgkm0<VM_AT_BARRIER>();
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                    copy_step(kt + NS, cur);
+                }
+                __builtin_amdgcn_s_waitcnt(0);
+            }
+            return;   // the epilogue has no barrier
+        }
+    }
+
+#pragma unroll 1
+    for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
         const _Float16 *const X = seg == 0 ? p.A : p.P;
         const _Float16 *const Y = seg == 0 ? p.B : p.Q;
         const int64_t ldx = seg == 0 ? p.lda : p.ldp;
@@ -354,10 +417,12 @@ gemm_bias_act_fast16(GemmArgs p)
         const int Kseg = seg == 0 ? p.K : p.K2;
         if (seg == 1) {
             __syncthreads();
-            if (p.sub && (NPW == 0 || !COPIES)) negate_acc();
+            if (p.sub) negate_acc();
         }
-        ca.init(ldx, ctid);
-        cb.init(ldy, ctid);
+        if constexpr (NPW == 0) {
+            ca.init(ldx, ctid);
+            cb.init(ldy, ctid);
+        }
 
         auto rsrc_a = [&](int k0) {
             if constexpr (TA) return make_rsrc(X + (int64_t)k0 * ldx + mc, MAX_RECORDS);
@@ -367,15 +432,8 @@ gemm_bias_act_fast16(GemmArgs p)
             if constexpr (TB) return make_rsrc(Y + (int64_t)k0 * ldy + nc, MAX_RECORDS);
             else return make_rsrc(Y + (int64_t)nc * ldy + k0, MAX_RECORDS);
         };
-        const int nk_seg = (Kseg + SK * BK - 1) / (SK * BK);
-        int s_lo = 0, s_hi = nk_seg;
-        if constexpr (SPLIT) {
-            const int off = seg == 0 ? 0 : (p.K + SK * BK - 1) / (SK * BK);
-            const int lo = kspl * p.split_steps - off, hi = lo + p.split_steps;
-            s_lo = __builtin_amdgcn_readfirstlane(lo < 0 ? 0 : (lo > nk_seg ? nk_seg : lo));
-            s_hi = __builtin_amdgcn_readfirstlane(hi < 0 ? 0 : (hi > nk_seg ? nk_seg : hi));
-        }
-        const int nk = s_hi - s_lo;
+        int s_lo, nk;
+        step_range(seg, Kseg, s_lo, nk);
 
         // Copies of step s: B straight into `stage`; A too, or (prologue)
         // into the registers ra (load_a, issued separately in the loop).
@@ -399,7 +457,7 @@ gemm_bias_act_fast16(GemmArgs p)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 load_a(s);
-                if (NPW ? COPIES : copy_wave) copy_step(s, mine + s * STAGE);
+                if (NPW == 0 && copy_wave) copy_step(s, mine + s * STAGE);
                 // the prologue writes step 0's left tile now; step 1's stays
                 // in registers until the first step's barrier
                 if (PROS && s == 0) relu_store_a(mine);
@@ -408,25 +466,8 @@ gemm_bias_act_fast16(GemmArgs p)
             wait_vm_lgkm0<(NS - 1) * NL>();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (NPW == 0 || !COPIES) {
-                read_a(0, mine, 0, 0);
-                read_b(0, mine, 0);
-            }
-        }
-        if constexpr (NPW > 0 && COPIES) {
-            // Copy-only waves: the barrier of every step, as the computing
-            // waves (step kt+1 landed, step kt's stage released), then the
-            // copies of step kt+NS into that stage.
-            for (int kt = 0; kt < nk; ++kt) {
-                char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
-                __builtin_amdgcn_sched_barrier(0);
-                wait_vm_lgkm0<VM_AT_BARRIER>();
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-                copy_step(kt + NS, cur);
-            }
-            __builtin_amdgcn_s_waitcnt(0);
-            return;
+            read_a(0, mine, 0, 0);
+            read_b(0, mine, 0);
         }
 
         // One reduction step.  On entry LDS stage `cur` holds step kt, steps
@@ -488,16 +529,7 @@ gemm_bias_act_fast16(GemmArgs p)
 
         __builtin_amdgcn_s_waitcnt(0);
         if (seg == 1 && p.sub) negate_acc();
-    };
-    if constexpr (NPW > 0) {
-        if (copy_wave) {   // done after the copies (the epilogue has no barrier)
-#pragma unroll 1
-            for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) segment(seg, std::true_type{});
-            return;
-        }
     }
-#pragma unroll 1
-    for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) segment(seg, std::bool_constant<NPW == 0>{});
     if constexpr (FOLD) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)
