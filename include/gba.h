@@ -208,6 +208,36 @@ gba_status gba_fused_workspace_size(const gba_fused_desc *desc, size_t *bytes);
  */
 gba_status gba_fused_tile(const gba_fused_desc *desc, int *tile);
 
+/* Kernel that runs a request: none (empty output), a tile of the fast path,
+ * a deep variant of one, the few-row kernel, the kernel for large requests
+ * outside the fast path, the general kernel. */
+typedef enum {
+    GBA_PATH_EMPTY = 0,
+    GBA_PATH_TILE = 1,
+    GBA_PATH_DEEP = 2,
+    GBA_PATH_FEW_ROWS = 3,
+    GBA_PATH_UNALIGNED = 4,
+    GBA_PATH_GENERAL = 5
+} gba_path;
+
+typedef struct gba_plan {
+    gba_path path;
+    int bm, bn;           /* outputs of a workgroup: bm rows x bn columns */
+    int splits;           /* workgroups each output tile's reduction is split across (1: not split) */
+    int threads;          /* of a workgroup */
+    int64_t workgroups;   /* of the launch (of a split's first launch) */
+} gba_plan;
+
+/*
+ * gba_fused_plan -- the kernel gba_fused_gemm would run the request on and
+ * its launch, given the workspace the descriptor carries (host-only
+ * computation, no GPU access).  For tests and measurements: which kernel
+ * runs a request is no part of its contract.
+ *
+ * Errors: as gba_fused_gemm's validation; GBA_EINVAL also for plan == NULL.
+ */
+gba_status gba_fused_plan(const gba_fused_desc *desc, gba_plan *plan);
+
 /*
  * gba_fused_gemm -- the four computation idioms of the paper's scope
  * (Introduction) in one kernel: a matmul with a pointwise prologue

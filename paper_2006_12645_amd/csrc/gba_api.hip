@@ -654,6 +654,17 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     return pl;
 }
 
+// Threads of a workgroup, and workgroups, of the plan's kernel (of a split
+// reduction the first one).
+int plan_threads(const gba_fused_desc &d, const Plan &pl)
+{
+    if (pl.thin.tm) return 64 * pl.thin.waves;
+    if (pl.tile < 0) return 64 * pl.cfg.wm * pl.cfg.wn;
+    return tile_threads(d.layoutA, d.layoutB, pl.cfg, d.accum == GBA_ACC_F16, d.prologue == GBA_PRO_RELU, pl.splits > 1);
+}
+
+int64_t plan_workgroups(const Plan &pl) { return pl.tiles_m * pl.tiles_n * pl.splits; }
+
 // The plan a validated request runs with, given the workspace it carries:
 // without room for the split the plan is made again without one (the
 // library's unsplit tile choice differs from its split one).
@@ -987,6 +998,23 @@ extern "C" gba_status gba_fused_tile(const gba_fused_desc *desc, int *tile)
     const gba_status st = validate(*desc);
     if (st != GBA_OK || desc->M == 0 || desc->N == 0) return st;
     *tile = plan_for(*desc).tile;
+    return GBA_OK;
+}
+
+extern "C" gba_status gba_fused_plan(const gba_fused_desc *desc, gba_plan *plan)
+{
+    if (desc == nullptr || plan == nullptr) return GBA_EINVAL;
+    *plan = gba_plan{};
+    const gba_status st = validate(*desc);
+    if (st != GBA_OK || desc->M == 0 || desc->N == 0) return st;
+    const Plan pl = plan_for(*desc);
+    plan->path = pl.thin.tm ? GBA_PATH_FEW_ROWS : pl.deep >= 0 ? GBA_PATH_DEEP : pl.tile >= 0 ? GBA_PATH_TILE
+                 : pl.ragged >= 0 ? GBA_PATH_UNALIGNED : GBA_PATH_GENERAL;
+    plan->bm = pl.thin.tm ? 16 * pl.thin.tm : pl.cfg.bm;
+    plan->bn = pl.thin.tm ? 16 * pl.thin.tn : pl.cfg.bn;
+    plan->splits = (int)pl.splits;
+    plan->threads = plan_threads(*desc, pl);
+    plan->workgroups = plan_workgroups(pl);
     return GBA_OK;
 }
 

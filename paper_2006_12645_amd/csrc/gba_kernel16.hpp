@@ -64,20 +64,16 @@ __device__ __forceinline__ int perm16(int t, int rho)
 // fragment reads and MFMAs: 4096 x 1024 x 8192 CR on 128x128 99.5 us with two
 // stages and no such waves (64x128 tile), 76.4 with.  The prologue rectifies
 // the fragments there (PROF below).
-template <int WM, int WN, int SK>
-constexpr int copy_only_waves()
-{
-    return (WM * WN < 8 && SK == 1) ? 4 : 0;
-}
+constexpr int copy_only_waves(int wm, int wn, int sk) { return wm * wn < 8 && sk == 1 ? 4 : 0; }
 
 template <int BM, int BN, int WM, int WN, int SK, int NSTG, int LA, int LB, bool ACC16, bool PRO, bool DUAL,
           bool SPLIT>
-__global__ void __launch_bounds__(64 * (WM * WN * SK + copy_only_waves<WM, WN, SK>()))
+__global__ void __launch_bounds__(64 * (WM * WN * SK + copy_only_waves(WM, WN, SK)))
 gemm_bias_act_fast16(GemmArgs p)
 {
     constexpr int NTG = 64 * WM * WN;         // threads per k-group
     constexpr int NT = NTG * SK;              // threads that compute
-    constexpr int NPW = copy_only_waves<WM, WN, SK>();
+    constexpr int NPW = copy_only_waves(WM, WN, SK);
     constexpr int BK = 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TM = WTM / 16, TN = WTN / 16;   // 16x16 blocks of the warp tile

@@ -133,6 +133,13 @@ constexpr bool use_fast16(int la, int lb, int bm, int bn, int wm, int wn, int sk
     return !pro && sk == 1 && nstg == 4 && layouts;
 }
 
+// Threads of a workgroup of a tile's kernel.
+constexpr int tile_threads(int la, int lb, const TileCfg &c, bool acc16, bool pro, bool split)
+{
+    const bool fast16 = use_fast16(la, lb, c.bm, c.bn, c.wm, c.wn, c.sk, c.nstg, acc16, pro, split);
+    return 64 * (c.wm * c.wn * c.sk + (fast16 ? copy_only_waves(c.wm, c.wn, c.sk) : 0));
+}
+
 // hipGetLastError reports the last failure of any runtime call on the
 // calling thread, not only of the launch before it: the launchers clear it
 // first, so that an earlier, unrelated failure does not turn a kernel that
@@ -144,9 +151,8 @@ template <int BM, int BN, int WM, int WN, int SK, int NSTG, int LA, int LB, bool
 hipError_t launch_fast(const GemmArgs &a, hipStream_t s)
 {
     // one workgroup per output tile, times the splits of its reduction
-    constexpr int NPW = use_fast16(LA, LB, BM, BN, WM, WN, SK, NSTG, ACC16, PRO, SPLIT)
-                            ? copy_only_waves<WM, WN, SK>() : 0;
-    dim3 grid((unsigned)(a.tiles_m * a.tiles_n * (SPLIT ? a.splits : 1))), block(64 * (WM * WN * SK + NPW));
+    constexpr int NT = tile_threads(LA, LB, TileCfg{BM, BN, WM, WN, SK, NSTG}, ACC16, PRO, SPLIT);
+    dim3 grid((unsigned)(a.tiles_m * a.tiles_n * (SPLIT ? a.splits : 1))), block(NT);
     // The 8-wave tiles (one k-group) run on 16x16x32 MFMAs, and so do the
     // four-stage small tiles where use_fast16 allows them;
     // everything else on 32x32x16 (measured per tile: the 16x16x32 kernels

@@ -41,6 +41,13 @@ class FusedDesc(ctypes.Structure):
                 ("split_k", _int), ("workspace", _vp), ("workspace_bytes", ctypes.c_size_t)]
 
 
+class Plan(ctypes.Structure):
+    """Mirror of struct gba_plan."""
+    _fields_ = [("path", _int), ("bm", _int), ("bn", _int), ("splits", _int), ("threads", _int), ("workgroups", _i64)]
+
+
+PATHS = ("empty", "tile", "deep", "few_rows", "unaligned", "general")  # enum gba_path
+
 # Every function include/gba.h declares, with its ctypes signature.
 _GEMM_ARGS = [_int, _int, _i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _vp, _i64, _int, _int]
 SIGNATURES = {
@@ -58,6 +65,7 @@ SIGNATURES = {
     "gba_fused_gemm_noalloc": (_int, [ctypes.POINTER(FusedDesc), _vp]),
     "gba_fused_workspace_size": (_int, [ctypes.POINTER(FusedDesc), ctypes.POINTER(ctypes.c_size_t)]),
     "gba_fused_tile": (_int, [ctypes.POINTER(FusedDesc), ctypes.POINTER(_int)]),
+    "gba_fused_plan": (_int, [ctypes.POINTER(FusedDesc), ctypes.POINTER(Plan)]),
     "gba_status_string": (_cp, [_int]),
     "gba_version": (_cp, []),
 }
@@ -241,6 +249,14 @@ def fused_tile(desc):
     t = _int(-1)
     _check(lib().gba_fused_tile(ctypes.byref(desc), ctypes.byref(t)), "gba_fused_tile")
     return t.value
+
+
+def fused_plan(desc):
+    """The Plan a filled FusedDesc would run with, its path as a name."""
+    p = Plan()
+    _check(lib().gba_fused_plan(ctypes.byref(desc), ctypes.byref(p)), "gba_fused_plan")
+    return {"path": PATHS[p.path], "bm": p.bm, "bn": p.bn, "splits": p.splits, "threads": p.threads,
+            "workgroups": p.workgroups}
 
 
 # Zero-filled workspaces, one per (device, stream): the library leaves every

@@ -1,0 +1,55 @@
+"""Which kernel the library runs a request on, through its host-only query
+gba_fused_plan (no GPU).  The measured choices name their times (MI355X,
+microseconds, operands in cache)."""
+import ctypes
+
+import pytest
+
+from paper_2006_12645_amd import gba
+
+FAKE = 0x10000  # 16-byte aligned, never dereferenced: the query does not touch memory
+LAYOUTS = {"RR": (0, 0), "RC": (0, 1), "CR": (1, 0), "CC": (1, 1)}
+MAX_THREADS = (1 << 32) - 1  # of one launch
+
+
+def desc(M, N, K, layout="RC", pad=0, accum="f32", prologue=False, K2=0, tile=-1, split=0, workspace=0):
+    la, lb = LAYOUTS[layout]
+    d = gba.new_desc()
+    d.layoutA, d.layoutB, d.M, d.N, d.K = la, lb, M, N, K
+    d.A, d.lda = FAKE, (K if la == 0 else M) + pad
+    d.B, d.ldb = FAKE, (N if lb == 0 else K) + pad
+    if K2:
+        d.second, d.K2 = gba.GBA_SECOND_ADD, K2
+        d.P, d.ldp = FAKE, (K2 if la == 0 else M) + pad
+        d.Q, d.ldq = FAKE, (N if lb == 0 else K2) + pad
+    d.prologue = gba.GBA_PRO_RELU if prologue else gba.GBA_PRO_NONE
+    d.bias_kind, d.bias = gba.GBA_BIAS_ROW, FAKE
+    d.act, d.C, d.ldc = gba.GBA_ACT_RELU, FAKE, N
+    d.accum = gba.ACCS[accum]
+    d.tile_id, d.split_k = tile, split
+    if workspace:
+        d.workspace, d.workspace_bytes = FAKE, workspace
+    return d
+
+
+def plan(*args, **kw):
+    return gba.fused_plan(desc(*args, **kw))
+
+
+def path(*args, **kw):
+    return plan(*args, **kw)["path"]
+
+
+def test_query():
+    assert path(0, 5, 5) == "empty"
+    assert plan(4096, 4096, 4096) == {"path": "tile", "bm": 256, "bn": 256, "splits": 1, "threads": 512,
+                                      "workgroups": 256}
+    assert plan(2048, 2048, 2048) == {"path": "deep", "bm": 128, "bn": 128, "splits": 1, "threads": 512,
+                                      "workgroups": 256}
+    assert path(4, 4096, 1024) == "few_rows" and path(4095, 4095, 4095) == "unaligned"
+    assert path(40, 300, 50, accum="f16") == "general"
+    p = plan(64, 512, 32768, workspace=16 << 20)
+    assert p["path"] == "tile" and p["splits"] > 1 and p["workgroups"] == 2 * 8 * p["splits"]
+    assert plan(64, 512, 32768)["splits"] == 1  # no workspace
+    assert gba.lib().gba_fused_plan(ctypes.byref(desc(8, 8, 8)), None) == gba.GBA_EINVAL
+    assert gba.lib().gba_fused_plan(ctypes.byref(desc(-1, 8, 8)), ctypes.byref(gba.Plan())) == gba.GBA_EINVAL
