@@ -446,6 +446,9 @@ const LayoutTable &table_for(int la, int lb, bool pro, bool dual)
     return lb == GBA_ROW_MAJOR ? variant_table<COL, ROW>(pro, dual) : variant_table<COL, COL>(pro, dual);
 }
 
+// Threads of one launch (grid times block) that the HIP runtime accepts.
+constexpr int64_t MAX_LAUNCH_THREADS = (int64_t(1) << 32) - 1;
+
 // Most workgroups one output tile's reduction is split across.
 constexpr int64_t MAX_SPLITS = 64;
 
@@ -508,6 +511,8 @@ constexpr int64_t THIN_MAX_LD = int64_t(1) << 23;
 //   * against the 64x64 tile of the kernel for requests outside the fast
 //     path: from K = 768 (RC 115 x 323 x 1311 9.7 -> 6.2, CR 148 x 919 x 1217
 //     10.1 -> 9.6, RR 221 x 709 x 431 6.0 against 7.6).
+//   * never a launch of 2^32 threads or more, which the runtime refuses: the
+//     general kernel needs 4 threads a column, the few-row one up to 32.
 ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
 {
     const ThinCfg none = {0, 0, 0};
@@ -535,7 +540,7 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
     // 22 us, 16 waves 26).
     const int64_t slabs = ceil_div(d.K, 64) + (has_second(d) ? ceil_div(d.K2, 64) : 0);
     c.waves = slabs < 8 ? 4 : slabs >= 64 && groups(c) <= 256 && c.tm + c.tn <= 3 ? 16 : 8;
-    return c;
+    return groups(c) * 64 * c.waves <= MAX_LAUNCH_THREADS ? c : none;
 }
 
 // The block tile of the kernel for large requests outside the fast path, or

@@ -53,3 +53,14 @@ def test_query():
     assert plan(64, 512, 32768)["splits"] == 1  # no workspace
     assert gba.lib().gba_fused_plan(ctypes.byref(desc(8, 8, 8)), None) == gba.GBA_EINVAL
     assert gba.lib().gba_fused_plan(ctypes.byref(desc(-1, 8, 8)), ctypes.byref(gba.Plan())) == gba.GBA_EINVAL
+
+
+@pytest.mark.parametrize("layout,M,N,K", [
+    ("RC", 1, 300_000_000, 8),     # 16 columns per 256 threads would be 4.8e9 threads
+    ("CC", 16, 140_000_000, 500),  # per 512
+    ("RR", 20, 600_000_000, 3), ("CR", 2, 1_000_000_000, 1)])
+def test_launch_of_few_rows_stays_in_the_runtimes_limit(layout, M, N, K):
+    """A launch has fewer than 2^32 threads; the general kernel, which took
+    these requests before the few-row kernel, needs 4 a column."""
+    p = plan(M, N, K, layout, pad=1)
+    assert p["threads"] * p["workgroups"] <= MAX_THREADS, p
