@@ -24,7 +24,10 @@
  *   - Calls are asynchronous: work is enqueued on `stream` (NULL = the null
  *     stream) and the function returns once the kernel is launched.
  *   - Arguments are validated on the host before anything is enqueued.  On
- *     any error nothing is launched and the output is left untouched.
+ *     any error nothing is launched and the output is left untouched (one
+ *     exception: when the runtime fails between the two launches of a split
+ *     reduction, GBA_EHIP, the workspace holds partial sums and has to be
+ *     zero-filled before it is used again).
  *   - Outputs must not alias inputs.
  *   - Inputs are expected to be finite.  The outputs for NaN or infinite
  *     inputs, and for results beyond the fp16 range, are not specified.
@@ -185,8 +188,10 @@ void gba_fused_desc_init(gba_fused_desc *desc);
  * zero again when it completes, so a workspace zero-filled once serves
  * any number of calls in stream order, whatever their shapes and tiles;
  * calls that may run at the same time need separate workspaces.  With a NULL
- * or smaller workspace the call runs unsplit.  split_k >= 2 asks for that many splits (fewer when
- * the reduction has fewer 64-deep steps); 0 lets the library decide.
+ * or smaller workspace, or when a launch of the split would have 2^32 threads
+ * or more, the call runs unsplit.  split_k >= 2 asks for that many splits
+ * (fewer when the reduction has fewer 64-deep steps); 0 lets the library
+ * decide.
  *
  * Errors: as gba_fused_gemm's validation; GBA_EINVAL also for bytes ==
  * NULL or split_k < 0.
@@ -278,7 +283,8 @@ gba_status gba_fused_plan(const gba_fused_desc *desc, gba_plan *plan);
  * (A/B when K > 0, P/Q when K2 > 0, bias when bias_kind != NONE, C),
  * split_k < 0, or a workspace not 256-byte aligned;
  * GBA_EUNSUPPORTED for M, N, K or K2 above 2^31-1 or pointers not 2-byte
- * aligned; GBA_EHIP if the launch fails.  Nothing is launched on error.
+ * aligned; GBA_EHIP if a launch fails.  Nothing is launched on error (but see
+ * the conventions above for a split).
  */
 gba_status gba_fused_gemm(const gba_fused_desc *desc, gba_stream_t stream);
 

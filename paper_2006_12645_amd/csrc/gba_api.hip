@@ -670,13 +670,24 @@ int plan_threads(const gba_fused_desc &d, const Plan &pl)
 
 int64_t plan_workgroups(const Plan &pl) { return pl.tiles_m * pl.tiles_n * pl.splits; }
 
+// Whether both launches of a split are within the runtime's limit (checked
+// before the first, since nothing may run on an error).
+bool split_launches_fit(const gba_fused_desc &d, const Plan &pl)
+{
+    const int64_t reduce_threads = pl.tiles_m * pl.tiles_n * ((int64_t)pl.cfg.bm * pl.cfg.bn / 4);
+    return plan_workgroups(pl) * plan_threads(d, pl) <= MAX_LAUNCH_THREADS && reduce_threads <= MAX_LAUNCH_THREADS;
+}
+
 // The plan a validated request runs with, given the workspace it carries:
-// without room for the split the plan is made again without one (the
-// library's unsplit tile choice differs from its split one).
+// without room for the split, or where its launches would not fit, the plan
+// is made again without one (the library's unsplit tile choice differs from
+// its split one).
 Plan plan_for(const gba_fused_desc &d)
 {
     Plan pl = make_plan(d, true);
-    if (pl.splits > 1 && (d.workspace == nullptr || d.workspace_bytes < pl.ws_bytes)) pl = make_plan(d, false);
+    if (pl.splits > 1 &&
+        (d.workspace == nullptr || d.workspace_bytes < pl.ws_bytes || !split_launches_fit(d, pl)))
+        pl = make_plan(d, false);
     return pl;
 }
 
@@ -992,7 +1003,8 @@ extern "C" gba_status gba_fused_workspace_size(const gba_fused_desc *desc, size_
     *bytes = 0;
     const gba_status st = validate(*desc);
     if (st != GBA_OK || desc->M == 0 || desc->N == 0) return st;
-    *bytes = make_plan(*desc, true).ws_bytes;
+    const Plan pl = make_plan(*desc, true);
+    if (pl.splits > 1 && split_launches_fit(*desc, pl)) *bytes = pl.ws_bytes;
     return GBA_OK;
 }
 

@@ -64,3 +64,16 @@ def test_launch_of_few_rows_stays_in_the_runtimes_limit(layout, M, N, K):
     these requests before the few-row kernel, needs 4 a column."""
     p = plan(M, N, K, layout, pad=1)
     assert p["threads"] * p["workgroups"] <= MAX_THREADS, p
+
+
+@pytest.mark.parametrize("tile,M,N,split", [(23, 16384, 16384, 64), (21, 32768, 16384, 64), (6, 262144, 65536, 2)])
+def test_split_whose_launches_do_not_fit_runs_unsplit(tile, M, N, split):
+    """Both launches of a split are checked before the first: tile 23 has 320
+    threads per 1024 outputs and split (268M outputs at 64 splits: 5.4e9), the
+    second kernel one per four outputs (2^34 of them: 2^32)."""
+    p = plan(M, N, 8192, tile=tile, split=split, workspace=1 << 60)
+    assert p["splits"] == 1 and p["threads"] * p["workgroups"] <= MAX_THREADS, p
+
+
+def test_largest_split_that_fits_is_kept():
+    assert plan(12288, 16384, 8192, tile=23, split=64, workspace=1 << 60)["splits"] == 64  # 4.03e9 threads
