@@ -621,7 +621,14 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
         pl.tile = select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro);
     else pl.tile = choose_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro, &pl.deep);
     if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = pl.deep = -1;
-    if (pl.tile < 0) pl.ragged = ragged_tile(d);
+    // No tile, no split: outside the fast path a long reduction over few
+    // outputs belongs to the few-row kernel (RC 412 x 173 x 16393 on 21
+    // workgroups of the 64x64 tile 90 us, on 143 of the few-row kernel 33; CC
+    // 295 x 241 x 61913 395 / 163; 150 such requests 2.8x, none slower).
+    if (pl.tile < 0) {
+        pl.ragged = ragged_tile(d);
+        auto_s = 1;
+    }
     // (a request for a split that the tile can make is kept)
     if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2))
         pl.thin = thin_cfg(d, pl.tile >= 0, pl.ragged >= 0);

@@ -66,6 +66,12 @@ def test_taken_from_the_tiles(M, N, K, K2, layout):
 
 
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
+@pytest.mark.parametrize("M,N,K,K2", [(64, 512, 16399, 0), (100, 100, 16400, 0), (65, 127, 9001, 8001)])
+def test_long_reductions_outside_the_fast_path(M, N, K, K2, layout):
+    check(M, N, K, layout, K2, prologue="relu" if K2 else None, bias="row", act="relu", seed=K)
+
+
+@pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 def test_empty_reduction_is_the_bias(layout):
     check(9, 80, 0, layout, bias="row", bias_op="sub", act="tanh")
 

@@ -77,3 +77,13 @@ def test_split_whose_launches_do_not_fit_runs_unsplit(tile, M, N, split):
 
 def test_largest_split_that_fits_is_kept():
     assert plan(12288, 16384, 8192, tile=23, split=64, workspace=1 << 60)["splits"] == 64  # 4.03e9 threads
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("M,N,K,pad", [(64, 512, 32767, 1), (64, 512, 32768, 1), (100, 100, 20000, 0), (128, 100, 40001, 0)])
+def test_long_reduction_outside_the_fast_path_is_spread_over_the_chip(M, N, K, pad, layout):
+    """It cannot be split across workgroups; on the 64x64 tile it would have
+    2 to 8 of them."""
+    for kw in ({}, {"workspace": 16 << 20}):
+        p = plan(M, N, K, layout, pad=pad, **kw)
+        assert p["path"] == "few_rows" and p["workgroups"] >= 28, p
