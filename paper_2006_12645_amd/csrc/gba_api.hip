@@ -615,11 +615,16 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     int64_t auto_s = 1;
     if (may_split && d.split_k == 0 && !tile_ok && fp32) auto_s = auto_splits(d.M, d.N, ktot);
     const bool pro = d.prologue == GBA_PRO_RELU;
+    const bool asked_split = may_split && d.split_k >= 2 && fp32;
     if (tile_ok) pl.tile = d.tile_id;
     else if (auto_s > 1) pl.tile = auto_split_tile(d);
-    else if (may_split && d.split_k >= 2)   // deep variants do not split
-        pl.tile = select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro);
-    else pl.tile = choose_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro, &pl.deep);
+    else {
+        // A requested split is kept where the rule's tile can make it (a
+        // k-group tile, a deep variant and the few-row kernel cannot).
+        pl.tile = asked_split ? select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro) : -1;
+        if (pl.tile < 0 || !tile_splits(TILES[pl.tile]))
+            pl.tile = choose_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro, &pl.deep);
+    }
     if (pl.tile >= 0 && !fast_path_ok(d)) pl.tile = pl.deep = -1;
     // No tile, no split: outside the fast path a long reduction over few
     // outputs belongs to the few-row kernel (RC 412 x 173 x 16393 on 21
@@ -629,8 +634,7 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
         pl.ragged = ragged_tile(d);
         auto_s = 1;
     }
-    // (a request for a split that the tile can make is kept)
-    if (!tile_ok && auto_s == 1 && (pl.tile < 0 || !may_split || d.split_k < 2))
+    if (!tile_ok && auto_s == 1 && !(asked_split && pl.tile >= 0 && pl.deep < 0 && tile_splits(TILES[pl.tile])))
         pl.thin = thin_cfg(d, pl.tile >= 0, pl.ragged >= 0);
     if (pl.thin.tm) pl.ragged = -1;
     pl.cfg = pl.deep >= 0 ? deep_cfg(d.layoutA, d.layoutB, pl.deep)

@@ -94,18 +94,26 @@ def test_infinite_operand_reaches_only_its_outputs():
 
 
 def test_split_request_still_splits():
-    """A request for a split across workgroups keeps it (same bits as the
-    entry point without a few-row kernel in the way: a forced tile)."""
-    A, B, bias = D.random_problem(65000, 64, 256, 4096)
-    dA, dB, db = U.device_operand(A, D.ROW), U.device_operand(B, D.COL), torch.from_numpy(bias).cuda()
-    t = gba.select_tile(64, 256, 4096)
-    d = gba.new_desc()
-    d.layoutB, d.M, d.N, d.K = gba.GBA_COL_MAJOR, 64, 256, 4096
-    d.A, d.lda, d.B, d.ldb = dA.data_ptr(), 4096, dB.data_ptr(), 4096
-    d.C, d.ldc = dA.data_ptr(), 256
-    d.split_k = 4
-    plain, forced = gba.workspace_size(d), None
-    d.tile_id = t
-    forced = gba.workspace_size(d)
-    assert plain == forced
-    U.assert_close(gba.fused_gemm(dA, dB, bias=db, split=4).cpu().numpy(), U.oracle_for(A, B, bias), what="split")
+    """A request for a split across workgroups that the rule's tile can make
+    keeps it (the same bits as on that tile, forced), where the few-row kernel
+    would otherwise run; one that the rule's tile cannot make does not keep
+    the few-row kernel away."""
+    for M, N, K, splits in ((64, 512, 1536, 4), (64, 256, 4096, 1)):
+        A, B, bias = D.random_problem(65000 + K, M, N, K)
+        dA, dB, db = U.device_operand(A, D.ROW), U.device_operand(B, D.COL), torch.from_numpy(bias).cuda()
+        t = gba.select_tile(M, N, K)
+        d = gba.new_desc()
+        d.layoutB, d.M, d.N, d.K = gba.GBA_COL_MAJOR, M, N, K
+        d.A, d.lda, d.B, d.ldb = dA.data_ptr(), K, dB.data_ptr(), K
+        d.C, d.ldc = dA.data_ptr(), N
+        unsplit = gba.fused_plan(d)
+        assert unsplit["path"] == "few_rows"
+        d.split_k, d.workspace, d.workspace_bytes = 4, dA.data_ptr(), 1 << 30
+        plain = gba.fused_plan(d)
+        assert plain["splits"] == splits and (gba.workspace_size(d) > 0) == (splits > 1)
+        got = gba.fused_gemm(dA, dB, bias=db, split=4)
+        if splits > 1:
+            assert torch.equal(got, gba.fused_gemm(dA, dB, bias=db, split=4, tile=t))
+        else:
+            assert plain == unsplit and torch.equal(got, gba.fused_gemm(dA, dB, bias=db))
+        U.assert_close(got.cpu().numpy(), U.oracle_for(A, B, bias), what="split")

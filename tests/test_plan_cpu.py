@@ -87,3 +87,18 @@ def test_long_reduction_outside_the_fast_path_is_spread_over_the_chip(M, N, K, p
     for kw in ({}, {"workspace": 16 << 20}):
         p = plan(M, N, K, layout, pad=pad, **kw)
         assert p["path"] == "few_rows" and p["workgroups"] >= 28, p
+
+
+def test_requested_split_is_kept_where_the_tile_can_make_it():
+    p = plan(64, 512, 1024, split=4, workspace=16 << 20)
+    assert p["path"] == "tile" and p["splits"] == 4, p
+    for kw in (dict(split=4), dict(split=4, accum="f16", workspace=16 << 20)):
+        assert plan(64, 512, 1024, **kw)["splits"] == 1, kw
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [("RC", 64, 256, 4096, "few_rows"),   # for a tile of four k-groups
+                                               ("RR", 3072, 320, 2496, "deep")])    # for one of two
+def test_requested_split_that_no_tile_can_make_changes_nothing(layout, M, N, K, want):
+    la, lb = LAYOUTS[layout]
+    p = plan(M, N, K, layout, split=4, workspace=1 << 30)
+    assert p == plan(M, N, K, layout) and p["path"] == want and p["splits"] == 1, p
