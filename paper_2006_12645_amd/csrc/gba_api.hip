@@ -484,17 +484,62 @@ struct ThinCfg {
 // Largest leading dimension the few-row kernel addresses with 32-bit offsets.
 constexpr int64_t THIN_MAX_LD = int64_t(1) << 23;
 
+// The few-row kernel's blocks: 16 tm rows by 16 tn columns, by B's layout (a
+// row-major B needs 64 bytes of each row to fill its loads).
+constexpr ThinCfg THIN_BLOCKS[2][3] = {{{1, 2, 0}, {1, 4, 0}, {2, 4, 0}}, {{1, 1, 0}, {1, 2, 0}, {2, 2, 0}}};
+
+// The blocks (index in THIN_BLOCKS) on which the few-row kernel beats the
+// general kernel, the only other one for a request that fits neither the
+// tiles nor the 64x64 tile of the kernel for requests outside the fast path;
+// -1: none.  pick: the smallest blocks that cover the output with one round
+// of 256 workgroups, or -1; slabs: 64-deep pieces of the reduction.  What
+// decides is the general kernel's chain of steps against the few-row
+// kernel's larger number of workgroups (3450 requests, many with operands
+// from HBM: 0.70x its time on these lines, 0.69x on the better of all).
+//   * smallest blocks: always.  1-16 x 4096 x 1024 RC 10.7 -> 4.1 us.
+//   * the middle ones from K = 8 (RR 14 x 8449 x 4 5.0 against 5.6 us, 8 x
+//     13535 x 56 5.8 -> 5.3), RC, where the general kernel copies straight,
+//     from three slabs (14 x 5238 x 37 4.4 against 5.2).
+//   * the largest from three slabs, CR from two, RC from nine (seven up to
+//     192 workgroups): RR 806 x 576 x 4 5.3 against 8.2, RC 22 x 8099 x 428
+//     7.7 / 8.4, 22 x 5838 x 497 8.0 -> 6.4.
+//   * fewer than 32 rows over more columns than that: as the columns grow the
+//     reduction must.  RC 9 x 47458 x 33 5.2 against 17.4, 11 x 20121 x 486
+//     8.7 / 18.3, 15 x 47066 x 4393 87 / 113, 4 x 8192 x 8192 96 -> 22 (6.1
+//     TB/s); CC 24 x 25091 x 484 14.1 / 29.3, 11 x 50184 x 928 80 -> 43.
+//     Row-major B takes the middle blocks up to 16 rows (RR 1 x 43509 x 48 6.8
+//     us in general, 16.2 on the smallest, 8.1 on these; 5 x 53525 x 457 41,
+//     33, 26).
+int thin_against_general(const gba_fused_desc &d, int pick, int64_t workgroups, int64_t slabs)
+{
+    const bool rowA = d.layoutA == GBA_ROW_MAJOR, colB = d.layoutB == GBA_COL_MAJOR, rc = rowA && colB;
+    const int64_t ktot = d.K + (has_second(d) ? d.K2 : 0);
+    if (pick == 0) return 0;
+    if (pick == 1) return (rc ? slabs >= 3 : ktot >= 8) ? 1 : -1;
+    if (pick == 2) return slabs >= (rc ? (workgroups <= 192 ? 7 : 9) : colB || rowA ? 3 : 2) ? 2 : -1;
+    if (d.M >= 32 || (!colB && d.N < 16 * THIN_BLOCKS[0][2].tn)) return -1;
+    const bool one = d.M <= 16;   // one block of rows
+    if (rc) {
+        const int64_t most = one ? (slabs > 48 ? 40960 : slabs > 32 ? 32768 : slabs > 16 ? 24576 : slabs > 12 ? 16384 : 0)
+                                 : (slabs > 32 ? 24576 : slabs > 16 ? 16384 : 0);
+        return d.N <= most ? (one ? 0 : 2) : -1;
+    }
+    if (colB) {
+        const int64_t least = d.N <= 16384 ? 3 : d.N <= 32768 ? 9 : 13;
+        return slabs >= least ? (one ? 0 : 2) : -1;
+    }
+    if (rowA) return slabs > (d.N > 32768 ? (one ? 7 : 8) : (one ? 2 : 6)) ? (one ? 1 : 2) : -1;
+    if (one || slabs <= 6) return slabs > 1 && (one || d.N <= 24576) ? 1 : -1;
+    return 2;
+}
+
 // Which requests (fp32 accumulation) the few-row kernel takes, and its
 // blocks.  Each of its workgroups streams its own panels of A and B with all
 // their reads in flight, which wins where one round of workgroups (256)
-// covers the output: the smallest blocks that do that, of 16x16, 16x32 and
-// 32x32 with column-major B, 16x32, 16x64 and 32x64 with row-major B (a
-// row-major B needs 64 bytes of each row to fill its loads).
-//   * fewer than 32 rows, where no tile fits: always (up to 16 rows the
-//     smallest blocks, else the largest, when none covers it in one round).
-//     1-16 x 4096 x 1024 RC 10.7 -> 4.1 us, 1-16 x 1024 x 4096 RC 34.6 ->
-//     5.9, RR 72 -> 7.4, CC 124 -> 6.6, 4 x 8192 x 8192 RC 96 -> 22 (6.1
-//     TB/s), RR 155 -> 29.
+// covers the output: the smallest blocks that do that.
+//   * where no tile fits (fewer than 32 rows among them) by
+//     thin_against_general.  1-16 x 1024 x 4096 RC 34.6 -> 5.9 us, RR 72 ->
+//     7.4, CC 124 -> 6.6.
 //   * from 32 rows on against the tiles, warm / operands from HBM: RC 32 x
 //     1024 x 4096 8.97 / 12.3 -> 6.1 / 8.2, 128 x 512 x 4096 9.1 / 9.6 ->
 //     6.5 / 6.8, RR 64 x 1024 x 4096 11.6 / 25.4 -> 8.2 / 16, 64 x 8192^2
@@ -521,24 +566,22 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
     if (has_second(d) && (d.ldp >= THIN_MAX_LD || d.ldq >= THIN_MAX_LD)) return none;
     const bool colB = d.layoutB == GBA_COL_MAJOR;
     const int64_t ktot = d.K + (has_second(d) ? d.K2 : 0);
-    static const ThinCfg blocks[2][3] = {{{1, 2, 0}, {1, 4, 0}, {2, 4, 0}}, {{1, 1, 0}, {1, 2, 0}, {2, 2, 0}}};
+    const int64_t slabs = ceil_div(d.K, 64) + (has_second(d) ? ceil_div(d.K2, 64) : 0);
     auto groups = [&](const ThinCfg &c) { return ceil_div(d.M, 16 * c.tm) * ceil_div(d.N, 16 * c.tn); };
-    auto fits = [&](const ThinCfg &c) { return colB || d.N >= 16 * c.tn; };
     int pick = -1;
     for (int b = 0; b < 3 && pick < 0; ++b)
-        if (fits(blocks[colB][b]) && groups(blocks[colB][b]) <= 256) pick = b;
+        if ((colB || d.N >= 16 * THIN_BLOCKS[colB][b].tn) && groups(THIN_BLOCKS[colB][b]) <= 256) pick = b;
     if (fast || ragged) {
         if (pick < 0 || ktot < (fast && (pick > 0 || d.layoutA == GBA_COL_MAJOR) ? 1536 : 768)) return none;
         if (fast && colB && pick == 2) return none;
-    } else if (pick < 0) {
-        if (d.M >= 32 || !fits(blocks[colB][2])) return none;
-        pick = d.M <= 16 ? 0 : 2;
+    } else {
+        pick = thin_against_general(d, pick, pick < 0 ? 0 : groups(THIN_BLOCKS[colB][pick]), slabs);
+        if (pick < 0) return none;
     }
-    ThinCfg c = blocks[colB][pick];
+    ThinCfg c = THIN_BLOCKS[colB][pick];
     // A wave takes at least one 64-deep slab; 16 waves pay from four each
     // while one round covers the output (512 workgroups, 8192^2: 8 waves
     // 22 us, 16 waves 26).
-    const int64_t slabs = ceil_div(d.K, 64) + (has_second(d) ? ceil_div(d.K2, 64) : 0);
     c.waves = slabs < 8 ? 4 : slabs >= 64 && groups(c) <= 256 && c.tm + c.tn <= 3 ? 16 : 8;
     return groups(c) * 64 * c.waves <= MAX_LAUNCH_THREADS ? c : none;
 }

@@ -48,6 +48,7 @@ def check(M, N, K, layout, K2=0, second="sub", prologue=None, bias="full", bias_
 @pytest.mark.parametrize("M,N,K,K2", [
     (1, 64, 64, 0), (1, 65, 1, 0), (16, 33, 63, 65), (17, 96, 65, 0), (31, 130, 129, 7),
     (5, 48, 300, 520), (3, 1000, 515, 0), (16, 47, 1100, 0), (24, 4112, 200, 0),
+    (7, 16473, 600, 0), (20, 16473, 300, 0),  # more columns than one round of any blocks covers
 ])
 def test_fewer_rows_than_any_tile(M, N, K, K2, layout):
     check(M, N, K, layout, K2, prologue="relu" if K2 else None, seed=M + N + K)

@@ -102,3 +102,34 @@ def test_requested_split_that_no_tile_can_make_changes_nothing(layout, M, N, K, 
     la, lb = LAYOUTS[layout]
     p = plan(M, N, K, layout, split=4, workspace=1 << 30)
     assert p == plan(M, N, K, layout) and p["path"] == want and p["splits"] == 1, p
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [
+    # (general, few rows: us)
+    ("RC", 9, 47458, 33, "general"),    # 5.2, 17.4
+    ("RC", 11, 20121, 486, "general"),  # 8.7, 18.3
+    ("RC", 15, 47066, 4393, "general"),  # 87, 113
+    ("CC", 24, 25091, 484, "general"),  # 14.1, 29.3
+    ("RR", 1, 43509, 48, "general"),    # 6.8, 16.2
+    ("RR", 806, 576, 4, "general"),     # 5.3, 8.2
+    ("RR", 14, 8449, 4, "general"),     # 5.0, 5.6
+    ("RC", 14, 5238, 37, "general"),    # 4.4, 5.2
+    ("RC", 22, 8099, 428, "general"),   # 7.7, 8.4
+    ("CR", 19, 46576, 292, "general"),  # 25.6, 32.6
+    ("RC", 1, 4096, 1024, "few_rows"),  # 10.7, 4.1
+    ("RC", 4, 8192, 8192, "few_rows"),  # 96, 22
+    ("RC", 22, 5838, 497, "few_rows"),  # 8.0, 6.4
+    ("CC", 11, 50184, 928, "few_rows"),  # 80, 43
+    ("RR", 8, 13535, 56, "few_rows"),   # 5.8, 5.3
+    ("RR", 5, 53525, 457, "few_rows"),  # 41, 26
+    ("CR", 20, 40577, 428, "few_rows"),  # 35.2, 36.0
+    ("CR", 30, 37922, 474, "few_rows"),  # 47.9, 31.5
+])
+def test_few_rows_against_the_general_kernel(layout, M, N, K, want):
+    assert path(M, N, K, layout, pad=1) == want
+
+
+def test_few_rows_over_many_columns_of_row_major_b_take_wider_blocks():
+    """RR 1 x 43509 x 48: 8.1 us on 16x64 blocks, 16.2 on 16x32."""
+    assert plan(5, 53525, 457, "RR", pad=1)["bn"] == 64 and plan(5, 16384, 457, "RR", pad=1)["bn"] == 64
+    assert plan(5, 8192, 457, "RR", pad=1)["bn"] == 32
