@@ -533,6 +533,11 @@ int thin_against_general(const gba_fused_desc &d, int pick, int64_t workgroups, 
     return 2;
 }
 
+// The shortest reduction (total) for which the few-row kernel takes a request
+// from the tiles, by row-major A, column-major B and blocks larger than the
+// smallest.
+constexpr int THIN_LEAST_K[2][2][2] = {{{1536, 3073}, {1536, 2561}}, {{768, 2561}, {1025, 2561}}};
+
 // Which requests (fp32 accumulation) the few-row kernel takes, and its
 // blocks.  Each of its workgroups streams its own panels of A and B with all
 // their reads in flight, which wins where one round of workgroups (256)
@@ -540,16 +545,17 @@ int thin_against_general(const gba_fused_desc &d, int pick, int64_t workgroups, 
 //   * where no tile fits (fewer than 32 rows among them) by
 //     thin_against_general.  1-16 x 1024 x 4096 RC 34.6 -> 5.9 us, RR 72 ->
 //     7.4, CC 124 -> 6.6.
-//   * from 32 rows on against the tiles, warm / operands from HBM: RC 32 x
-//     1024 x 4096 8.97 / 12.3 -> 6.1 / 8.2, 128 x 512 x 4096 9.1 / 9.6 ->
-//     6.5 / 6.8, RR 64 x 1024 x 4096 11.6 / 25.4 -> 8.2 / 16, 64 x 8192^2
-//     39 / 54 -> 34 / 44, 256 x 256 x 4096 RC 9.3 / 9.6 -> 6.6 / 6.8, CC 48 x
-//     2048^2 7.8 / 11.9 -> 6.1 / 8.7.  The tiles' start-up is shorter: RC
-//     256 x 256 x 1024 4.6 / 5.3 -> 4.2 / 4.6 but 200 x 264 x 648 4.1 / 4.7
-//     against 4.4 / 4.8, so the smallest blocks from K = 768; RC 96 x 1000^2
-//     on 16x32 blocks 4.6 / 5.4 against 4.9 / 5.7 and CR 48 x 1000^2 5.8 /
-//     7.5 against 6.8 / 9.7, so the larger blocks, and any with a
-//     column-major A (read element-wise), from K = 1536.
+//   * from 32 rows on against the tiles, from the K that THIN_LEAST_K gives:
+//     the tiles' start-up is shorter, and a column-major A is read
+//     element-wise here (2450 requests of up to 600000 outputs, warm or with
+//     operands from HBM: 0.861x the tiles' time, 0.854x on the better of the
+//     two; 17 lose more than 5%).  Warm / operands from HBM: RC 32 x 1024 x
+//     4096 8.97 / 12.3 -> 6.1 / 8.2, RR 64 x 1024 x 4096 11.6 / 25.4 -> 8.2 /
+//     16, 64 x 8192^2 39 / 54 -> 34 / 44, 256 x 256 x 4096 RC 9.3 / 9.6 -> 6.6
+//     / 6.8, CC 48 x 2048^2 7.8 / 11.9 -> 6.1 / 8.7.  Below the limits: RC 200
+//     x 264 x 648 4.1 / 4.7 against 4.4 / 4.8, RR 656 x 624 x 1624 10.3 /
+//     11.3 (warm), CR 872 x 576 x 2424 16.4 / 19.7 (warm), 224 x 1568 x 2680
+//     16.8 / 19.9 (warm).
 //     With column-major B the tiles keep what needs 32x32 blocks (RC 128 x
 //     2048^2 6.6 / 8.5 against 7.7 / 9.5, CC 320 x 704 x 2880 13.2 / 13.1
 //     against 15.2 / 15.0).
@@ -571,9 +577,16 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
     int pick = -1;
     for (int b = 0; b < 3 && pick < 0; ++b)
         if ((colB || d.N >= 16 * THIN_BLOCKS[colB][b].tn) && groups(THIN_BLOCKS[colB][b]) <= 256) pick = b;
-    if (fast || ragged) {
-        if (pick < 0 || ktot < (fast && (pick > 0 || d.layoutA == GBA_COL_MAJOR) ? 1536 : 768)) return none;
-        if (fast && colB && pick == 2) return none;
+    if (fast) {
+        const bool rowA = d.layoutA == GBA_ROW_MAJOR;
+        if (pick < 0 || (colB && pick == 2)) return none;
+        int64_t least = THIN_LEAST_K[rowA][colB][pick > 0];
+        if (pick > 0 && d.M <= 48) least = 1536;   // the tiles pad more
+        if (rowA && colB && d.prologue == GBA_PRO_RELU) least = pick == 0 ? 768 : 1536;   // tiles without copy-only waves
+        if (!rowA && !colB && pick == 0 && groups(THIN_BLOCKS[0][0]) > 128) least = 2049;
+        if (ktot < least) return none;
+    } else if (ragged) {
+        if (pick < 0 || ktot < 768) return none;
     } else {
         pick = thin_against_general(d, pick, pick < 0 ? 0 : groups(THIN_BLOCKS[colB][pick]), slabs);
         if (pick < 0) return none;

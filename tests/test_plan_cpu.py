@@ -133,3 +133,18 @@ def test_few_rows_over_many_columns_of_row_major_b_take_wider_blocks():
     """RR 1 x 43509 x 48: 8.1 us on 16x64 blocks, 16.2 on 16x32."""
     assert plan(5, 53525, 457, "RR", pad=1)["bn"] == 64 and plan(5, 16384, 457, "RR", pad=1)["bn"] == 64
     assert plan(5, 8192, 457, "RR", pad=1)["bn"] == 32
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [
+    # (tiles, few rows: us)
+    ("RC", 256, 256, 1024, "tile"), ("RC", 256, 256, 1152, "few_rows"),  # 4.2, 4.6 at 1024; 9.3, 6.6 at 4096
+    ("RR", 656, 624, 1624, "tile"),     # 10.3, 11.3
+    ("RR", 64, 1024, 4096, "few_rows"),  # 11.6, 8.2
+    ("CR", 872, 576, 2424, "tile"),     # 16.4, 19.7
+    ("CR", 224, 1568, 2680, "tile"),    # 16.8, 19.9
+    ("CR", 1472, 224, 1696, "tile"),    # 10.2, 12.5
+    ("CC", 48, 2048, 2048, "few_rows"),  # 7.8, 6.1
+    ("CC", 72, 1536, 1784, "tile"),     # 8.5, 9.8
+])
+def test_few_rows_against_the_tiles(layout, M, N, K, want):
+    assert path(M, N, K, layout) == want
