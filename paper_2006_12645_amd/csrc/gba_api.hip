@@ -186,14 +186,20 @@ int select_tile(int64_t M, int64_t N, int64_t K, int accum, int la, int lb, bool
         } else if (la == lb && !pro) {
             // RR and CC: the four-stage tile with its long side along the
             // operand's contiguous direction (32x128 in RR, 128x32 in CC)
-            // up to one workgroup per compute unit, from K = 1024 two, else
-            // the 8-wave tiles below.  With its 32x32 warp tiles (four computing waves) it
-            // takes 1088 x 1792 x 3072 RR (476 workgroups) in 31.4 us against
-            // 37.1 on the 8-wave 64x128 tile (from HBM 34.8 / 45.3), 4032 x
-            // 320 x 4544 CC (320) 37.7 / 49.2 (40.7 / 62.6); 4864 x 704 x
-            // 2112 RR (912) 43.6 / 33.0, 896 x 1472 x 576 CC (322) 9.0 / 7.8.
+            // up to one workgroup per compute unit, over longer reductions
+            // up to two, else the 8-wave tiles below.  The second workgroup
+            // pays the longer the reduction, the sooner the larger the output
+            // side it is long on: from K * K * side = 2e9 (899 requests of
+            // 257 to 512 workgroups: 0.89x the 8-wave tiles' time, 16 more
+            // than 1.05x; 190 with K = 1024 as the line).  1088 x 1792 x 3072
+            // RR 31.4 us against 37.1 on the 8-wave 64x128 tile (from HBM
+            // 34.8 / 45.3), 4032 x 320 x 4544 CC 37.7 / 49.2 (40.7 / 62.6);
+            // RR 3488 x 376 x 1352 16.5 / 14.0, 2904 x 272 x 1976 20.0 / 17.7,
+            // CC 432 x 3112 x 1216 14.9 / 13.7; 4864 x 704 x 2112 RR (912
+            // workgroups) 43.6 / 33.0.
             const int tn = la == GBA_ROW_MAJOR ? 24 : 25;
-            if (tile_fits(tn, M, N) && tiles(tn) <= (K >= 1024 ? 512 : 256)) return tn;
+            const bool two_rounds = K >= 1024 && (double)K * K * (la == GBA_ROW_MAJOR ? N : M) >= 2e9;
+            if (tile_fits(tn, M, N) && tiles(tn) <= (two_rounds ? 512 : 256)) return tn;
             if (ai < RIDGE_AI && (M <= 256 || N <= 256) && tile_fits(8, M, N) && tiles(8) <= 256) return 8;
         } else if (la == lb) {
             // RR and CC with the prologue, where those tiles have no

@@ -148,3 +148,21 @@ def test_few_rows_over_many_columns_of_row_major_b_take_wider_blocks():
 ])
 def test_few_rows_against_the_tiles(layout, M, N, K, want):
     assert path(M, N, K, layout) == want
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [
+    # fp16 accumulation, two workgroups of the four-stage tile per compute
+    # unit against the 8-wave tile (us)
+    ("RR", 1088, 1792, 3072, 24),  # 31.4, 37.1
+    ("RR", 1144, 1120, 1544, 24),  # 17.7, 20.9
+    ("RR", 2872, 408, 2240, 24),   # 22.7, 26.7 at K = 2040
+    ("RR", 3488, 376, 1352, 20),   # 16.5, 14.0
+    ("RR", 2904, 272, 1976, 20),   # 20.0, 17.7
+    ("CC", 4032, 320, 4544, 25),   # 37.7, 49.2
+    ("CC", 432, 3112, 1216, 19),   # 14.9, 13.7
+    ("CC", 1400, 1032, 1656, 25),  # 20.4, 24.7
+    ("RR", 1000, 1000, 512, 24),   # one workgroup per compute unit
+])
+def test_fp16_four_stage_tile_on_two_rounds(layout, M, N, K, want):
+    la, lb = LAYOUTS[layout]
+    assert gba.select_tile(M, N, K, la, lb, accum="f16") == want
