@@ -611,18 +611,23 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
 //   * 64x64 while two per compute unit cover the output (512 of them), then
 //     128x128: RC 289 x 6103 x 1437 (480 64x64 tiles) 20.7 / 22.2 us, 755 x
 //     2797 x 577 (528) 16.4 / 13.2, 513 x 4097 x 1001 (585) 23.3 / 18.7.
-//   * 256x256 by the two's times: 15 us + 2 us a 64-deep step for a round
-//     of 256 workgroups against 7 us + 1.4 us for a round of 512 128x128
-//     ones, of which a part-filled last round costs about half: RC 3081 x
-//     3061 x 1933 (156 of 256x256, 600 of 128x128) 67 / 75 us, 4095^3 (256,
-//     1024) 139 / 190, RR 8191 x 1023 x 4095 (128, 512) 120 / 99, CC 3429 x
-//     4717 x 1417 (266, 999) 109 / 86, RC 7247 x 5889 x 177 (696, 2679) 77 /
-//     69.
+//   * 256x256 (fp32 accumulation) by the two's times: 15 us + 2 us a 64-deep
+//     step for a round of 256 workgroups against 7 us + 1.4 us for a round of
+//     512 128x128 ones, of which a part-filled last round costs about half:
+//     RC 3081 x 3061 x 1933 (156 of 256x256, 600 of 128x128) 67 / 75 us, RR
+//     8191 x 1023 x 4095 (128, 512) 120 / 99, CC 3429 x 4717 x 1417 (266, 999)
+//     109 / 86, RC 7247 x 5889 x 177 (696, 2679) 77 / 69.  With fp16
+//     accumulation its sums do not fit in registers (100 and more spilled):
+//     twice the 128x128 tile's time at every size (CR 1968 x 4802 x 1728 166 /
+//     77, RC 3615 x 3221 x 896 100 and on the general kernel 74), so it is not
+//     built.
 //   * the general kernel, whose workgroups fit five to a compute unit, where
 //     two to three steps cover little more than two rounds of 64x64 tiles
 //     and it copies straight (RC): 411 x 4739 x 137 (525) 7.7 us against
 //     8.6 on 128x128, 1559 x 1713 x 71 (675) 7.2 / 7.6; but 1079 x 1911 x 71
-//     (510) 6.7 -> 6.4 on 64x64.
+//     (510) 6.7 -> 6.4 on 64x64.  With fp16 accumulation up to three steps of
+//     any of these: RC 325 x 73 x 64 4.6 / 5.4, 2032 x 210 x 96 5.2 / 5.9, 1352
+//     x 2119 x 96 7.6 / 9.2.
 // Before (general kernel): RC 4095^3 350 us, RR 665, CR 1164, CC 957; 1023^3
 // 14.4 to 63.5, now 9.6 to 10.4.
 int ragged_tile(const gba_fused_desc &d)
@@ -640,8 +645,9 @@ int ragged_tile(const gba_fused_desc &d)
     const double nk = ceil_div(d.K, 64) + (two ? ceil_div(d.K2, 64) : 0);
     const double cost0 = (15 + 2 * nk) * ceil_div(t0, 256);
     const double cost1 = (7 + 1.4 * nk) * 0.5 * (ceil_div(t1, 512) + t1 / 512.0);
-    if (d.layoutA == GBA_ROW_MAJOR && d.layoutB == GBA_COL_MAJOR && nk <= 3 && t2 > 512 && t2 <= 700) return -1;
-    if (t0 >= 136 && cost0 <= cost1) return 0;
+    const bool rc = d.layoutA == GBA_ROW_MAJOR && d.layoutB == GBA_COL_MAJOR;
+    if (rc && nk <= 3 && (acc16 ? t2 <= 1600 : t2 > 512 && t2 <= 700)) return -1;
+    if (!acc16 && t0 >= 136 && cost0 <= cost1) return 0;
     if (t1 > 0 && t2 > 512) return 1;
     return t2 > 0 ? 2 : -1;
 }

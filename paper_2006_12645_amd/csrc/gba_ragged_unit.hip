@@ -10,7 +10,7 @@
 namespace gba {
 
 #define GBA_RAGGED_ENTRY(id, BM, BN, WM, WN) \
-    {&launch_ragged<BM, BN, WM, WN, GBA_LA, GBA_LB, false>, &launch_ragged<BM, BN, WM, WN, GBA_LA, GBA_LB, true>},
+    {&launch_ragged<BM, BN, WM, WN, GBA_LA, GBA_LB, false>, ragged_acc16<BM, BN, WM, WN, GBA_LA, GBA_LB>()},
 
 template <>
 LaunchFn ragged_entry<GBA_LA, GBA_LB>(int acc16, int tile)

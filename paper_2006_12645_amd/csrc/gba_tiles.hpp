@@ -243,6 +243,14 @@ hipError_t launch_ragged(const GemmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Launch-table entry for fp16 accumulation: none on the 256x256 tile.
+template <int BM, int BN, int WM, int WN, int LA, int LB>
+constexpr LaunchFn ragged_acc16()
+{
+    if constexpr (BM * BN <= 128 * 128) return &launch_ragged<BM, BN, WM, WN, LA, LB, true>;
+    else return nullptr;
+}
+
 template <int LA, int LB>
 LaunchFn ragged_entry(int acc16, int tile);
 

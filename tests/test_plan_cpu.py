@@ -166,3 +166,17 @@ def test_few_rows_against_the_tiles(layout, M, N, K, want):
 def test_fp16_four_stage_tile_on_two_rounds(layout, M, N, K, want):
     la, lb = LAYOUTS[layout]
     assert gba.select_tile(M, N, K, la, lb, accum="f16") == want
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [
+    # fp16 accumulation outside the fast path (us)
+    ("CR", 1968, 4802, 1728, 128),  # 166 on 256x256, 77
+    ("RC", 3615, 3221, 896, 128),   # 100 on 256x256
+    ("RC", 4095, 4095, 4096, 128),
+    ("RC", 325, 73, 64, "general"),  # 4.6, 5.4 on 64x64
+    ("RC", 1352, 2119, 96, "general"),  # 7.6, 9.2 on 128x128
+    ("RR", 325, 73, 64, 64), ("RC", 325, 73, 320, 64),
+])
+def test_unaligned_fp16(layout, M, N, K, want):
+    p = plan(M, N, K, layout, pad=1, accum="f16")
+    assert p["path"] == want if want == "general" else (p["path"], p["bm"]) == ("unaligned", want), p
