@@ -616,7 +616,11 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
 //     512 128x128 ones, of which a part-filled last round costs about half:
 //     RC 3081 x 3061 x 1933 (156 of 256x256, 600 of 128x128) 67 / 75 us, RR
 //     8191 x 1023 x 4095 (128, 512) 120 / 99, CC 3429 x 4717 x 1417 (266, 999)
-//     109 / 86, RC 7247 x 5889 x 177 (696, 2679) 77 / 69.  With fp16
+//     109 / 86, RC 7247 x 5889 x 177 (696, 2679) 77 / 69.  In CC, where it
+//     spills in its loop, the 256x256 tile takes a fifth more (3081 x 3061 x
+//     1933 88 / 67, 2082 x 5583 x 1221 63 / 51, 4095^3 174 / 192).  250
+//     requests of 100 to 700 of its tiles: within 0.1-0.6% of the better of
+//     the two in every layout.  With fp16
 //     accumulation its sums do not fit in registers (100 and more spilled):
 //     twice the 128x128 tile's time at every size (CR 1968 x 4802 x 1728 166 /
 //     77, RC 3615 x 3221 x 896 100 and on the general kernel 74), so it is not
@@ -643,7 +647,8 @@ int ragged_tile(const gba_fused_desc &d)
     };
     const int64_t t0 = tiles(0), t1 = tiles(1), t2 = tiles(2);
     const double nk = ceil_div(d.K, 64) + (two ? ceil_div(d.K2, 64) : 0);
-    const double cost0 = (15 + 2 * nk) * ceil_div(t0, 256);
+    const bool cc = d.layoutA == GBA_COL_MAJOR && d.layoutB == GBA_COL_MAJOR;
+    const double cost0 = (cc ? 1.2 : 1.0) * (15 + 2 * nk) * ceil_div(t0, 256);
     const double cost1 = (7 + 1.4 * nk) * 0.5 * (ceil_div(t1, 512) + t1 / 512.0);
     const bool rc = d.layoutA == GBA_ROW_MAJOR && d.layoutB == GBA_COL_MAJOR;
     if (rc && nk <= 3 && (acc16 ? t2 <= 1600 : t2 > 512 && t2 <= 700)) return -1;

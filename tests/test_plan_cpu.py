@@ -180,3 +180,15 @@ def test_fp16_four_stage_tile_on_two_rounds(layout, M, N, K, want):
 def test_unaligned_fp16(layout, M, N, K, want):
     p = plan(M, N, K, layout, pad=1, accum="f16")
     assert p["path"] == want if want == "general" else (p["path"], p["bm"]) == ("unaligned", want), p
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", [
+    # 256x256, 128x128 (us)
+    ("CC", 3081, 3061, 1933, 128),  # 88, 67
+    ("CC", 2082, 5583, 1221, 128),  # 63, 51
+    ("CC", 4095, 4095, 4095, 256),  # 174, 192
+    ("RC", 3081, 3061, 1933, 256),  # 64, 69
+    ("RC", 4095, 4095, 4095, 256),  # 142, 195
+])
+def test_unaligned_256x256_tile(layout, M, N, K, want):
+    assert plan(M, N, K, layout, pad=1)["bm"] == want
