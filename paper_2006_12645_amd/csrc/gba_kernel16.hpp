@@ -338,193 +338,35 @@ gemm_bias_act_fast16(GemmArgs p)
         }
     }
 
-    // The steps [s_lo, s_lo + nk) of a product that this workgroup reduces.
-    auto step_range = [&](int seg, int Kseg, int &lo_out, int &nk) {
-        const int nk_seg = (Kseg + SK * BK - 1) / (SK * BK);
-        int s_lo = 0, s_hi = nk_seg;
-        if constexpr (SPLIT) {
-            const int off = seg == 0 ? 0 : (p.K + SK * BK - 1) / (SK * BK);
-            const int lo = kspl * p.split_steps - off, hi = lo + p.split_steps;
-            s_lo = __builtin_amdgcn_readfirstlane(lo < 0 ? 0 : (lo > nk_seg ? nk_seg : lo));
-            s_hi = __builtin_amdgcn_readfirstlane(hi < 0 ? 0 : (hi > nk_seg ? nk_seg : hi));
-        }
-        lo_out = s_lo;
-        nk = s_hi - s_lo;
+    // The products' reductions, whose body is gba_kernel16_product.inc.  With
+    // copy-only waves each kind of wave has its own instance of it (COPIES:
+    // the copying one), so that the accumulators are not merged with a path
+    // that has none.  Without them it is a plain loop: as an instance too it
+    // made the 256x256 kernels spill more (CR fp32 12 registers against 6:
+    // 7320 x 4528 x 144 43.7 us against 38.7).  The branches stand one after
+    // the other as they do so that the second product's arguments are loaded
+    // at the start with the others: loaded on each path, they cost the kernels
+    // of two products with copy-only waves 0.8 us.
+    auto product = [&](int seg, auto copies) {
+        constexpr bool COPIES = decltype(copies)::value;
+#include "gba_kernel16_product.inc"
     };
-
-    // Copy-only waves: the barriers of the computing waves (the first step
-    // landed, then at every step: step kt+1 landed, step kt's stage released),
-    // after each of the latter the copies of step kt+NS into that stage.  A
-    // loop of their own, so that the accumulators are not merged with a path
-    // that has none; the shared loop below stays a plain one, since as a
-    // lambda called for either kind of wave it made the 256x256 kernels
-    // without such waves spill more (CR fp32 12 registers against 6: 5176 x
-    // 4456 x 128 27.9 us against 25.3).
     if constexpr (NPW > 0) {
-        if (copy_wave) {
+        if (copy_wave) {   // done after the copies (the epilogue has no barrier)
 #pragma unroll 1
-            for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
-                const _Float16 *const X = seg == 0 ? p.A : p.P;
-                const _Float16 *const Y = seg == 0 ? p.B : p.Q;
-                const int64_t ldx = seg == 0 ? p.lda : p.ldp;
-                const int64_t ldy = seg == 0 ? p.ldb : p.ldq;
-                const int Kseg = seg == 0 ? p.K : p.K2;
-                int s_lo, nk;
-                step_range(seg, Kseg, s_lo, nk);
-                if (seg == 1) __syncthreads();
-                ca.init(ldx, ctid);
-                cb.init(ldy, ctid);
-                auto copy_step = [&](int s, char *stage) {
-                    const int k0 = __builtin_amdgcn_readfirstlane(((s < nk ? s : nk - 1) + s_lo) * BK);
-                    const int kleft = s < nk ? Kseg - k0 : 0;
-                    ca.dma(make_rsrc(X + (TA ? (int64_t)k0 * ldx + mc : (int64_t)mc * ldx + k0), MAX_RECORDS), stage,
-                           kleft);
-                    cb.dma(make_rsrc(Y + (TB ? (int64_t)k0 * ldy + nc : (int64_t)nc * ldy + k0), MAX_RECORDS),
-                           stage + BM * ROWB, kleft);
-                };
-                if (nk > 0) {
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) copy_step(s, mine + s * STAGE);
-                    __builtin_amdgcn_sched_barrier(0);
-                    wait_vm_lgkm0<(NS - 1) * NL>();
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                for (int kt = 0; kt < nk; ++kt) {
-                    char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
-                    __builtin_amdgcn_sched_barrier(0);
-                    wait_vm_lgkm0<VM_AT_BARRIER>();
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_sched_barrier(0);
-                    copy_step(kt + NS, cur);
-                }
-                __builtin_amdgcn_s_waitcnt(0);
-            }
-            return;   // the epilogue has no barrier
+            for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) product(seg, std::true_type{});
+            return;
         }
     }
-
+    if constexpr (NPW > 0) {
 #pragma unroll 1
-    for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
-        const _Float16 *const X = seg == 0 ? p.A : p.P;
-        const _Float16 *const Y = seg == 0 ? p.B : p.Q;
-        const int64_t ldx = seg == 0 ? p.lda : p.ldp;
-        const int64_t ldy = seg == 0 ? p.ldb : p.ldq;
-        const int Kseg = seg == 0 ? p.K : p.K2;
-        if (seg == 1) {
-            __syncthreads();
-            if (p.sub) negate_acc();
+        for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) product(seg, std::false_type{});
+    } else {
+#pragma unroll 1
+        for (int seg = 0; seg < (DUAL ? 2 : 1); ++seg) {
+            constexpr bool COPIES = true;
+#include "gba_kernel16_product.inc"
         }
-        if constexpr (NPW == 0) {
-            ca.init(ldx, ctid);
-            cb.init(ldy, ctid);
-        }
-
-        auto rsrc_a = [&](int k0) {
-            if constexpr (TA) return make_rsrc(X + (int64_t)k0 * ldx + mc, MAX_RECORDS);
-            else return make_rsrc(X + (int64_t)mc * ldx + k0, MAX_RECORDS);
-        };
-        auto rsrc_b = [&](int k0) {
-            if constexpr (TB) return make_rsrc(Y + (int64_t)k0 * ldy + nc, MAX_RECORDS);
-            else return make_rsrc(Y + (int64_t)nc * ldy + k0, MAX_RECORDS);
-        };
-        int s_lo, nk;
-        step_range(seg, Kseg, s_lo, nk);
-
-        // Copies of step s: B straight into `stage`; A too, or (prologue)
-        // into the registers ra (load_a, issued separately in the loop).
-        auto step_k0 = [&](int s) {
-            return __builtin_amdgcn_readfirstlane((((s < nk ? s : nk - 1) + s_lo) * SK + grp) * BK);
-        };
-        auto load_a = [&](int s) {
-            if constexpr (PROS) {
-                const int k0 = step_k0(s);
-                ca.load(rsrc_a(k0), s < nk ? Kseg - k0 : 0, ra);
-            }
-        };
-        auto copy_step = [&](int s, char *stage) {
-            const int k0 = step_k0(s);
-            const int kleft = s < nk ? Kseg - k0 : 0;
-            if constexpr (!PROS) ca.dma(rsrc_a(k0), stage, kleft);
-            cb.dma(rsrc_b(k0), stage + BM * ROWB, kleft);
-        };
-
-        if (nk > 0) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                load_a(s);
-                if (NPW == 0 && copy_wave) copy_step(s, mine + s * STAGE);
-                // the prologue writes step 0's left tile now; step 1's stays
-                // in registers until the first step's barrier
-                if (PROS && s == 0) relu_store_a(mine);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            wait_vm_lgkm0<(NS - 1) * NL>();
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            read_a(0, mine, 0, 0);
-            read_b(0, mine, 0);
-        }
-
-        // One reduction step.  On entry LDS stage `cur` holds step kt, steps
-        // kt+1 .. kt+NS-1 are under way into the other stages, fa[0] holds
-        // the A fragments of slice 0 and fb[0] the B fragments of half 0.
-        // (two instances of the loop: with the copies, for the waves that
-        // issue them, and without)
-        auto run_loop = [&](auto with_copies) {
-        constexpr bool WC = decltype(with_copies)::value;
-        for (int kt = 0; kt < nk; ++kt) {
-            char *cur = mine + (int)((unsigned)kt % NS) * STAGE;
-            char *nxt = mine + (int)((unsigned)(kt + 1) % NS) * STAGE;
-            // slice 0: half 0, first A blocks
-            read_a(1, cur, 0, 1);
-            if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
-            mfmas(0, 0, 0);
-            sched_slice<NM, NRA, 0, 0, false>();
-            // slice 1: half 0, second A blocks (B fragments of half 1 in flight)
-            read_a(0, cur, 1, 0);
-            read_b(1, cur, 1);
-            mfmas(1, 0, 1);
-            round16();
-            sched_slice<NM, NRB, 0, 0, false>();
-            // slice 2: half 1, first A blocks (prologue: plus step kt+1's
-            // rectified left tile into its stage, whose loads were issued
-            // three slices ago; kept inside this slice so that the wait for
-            // them is not hoisted to the top of the step)
-            if constexpr (PROS) __builtin_amdgcn_sched_barrier(0);
-            read_a(1, cur, 1, 1);
-            relu_store_a(nxt);
-            load_a(kt + NS);
-            mfmas(0, 1, 0);
-            if constexpr (PROS) sched_slice2<NM, NRA, 0x200, CopyA::NLOAD, 0x020, CopyA::NLOAD>();
-            else sched_slice<NM, NRA, 0, 0, false>();
-            if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
-            // Step kt+1 complete in LDS for every wave; every read of `cur` done.
-            if constexpr (VM_AT_BARRIER == 0) {
-                __builtin_amdgcn_s_waitcnt(0);
-                __syncthreads();
-            } else {
-                __builtin_amdgcn_sched_barrier(0);
-                wait_vm_lgkm0<VM_AT_BARRIER>();
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // slice 3: half 1, second A blocks, plus the first fragments of
-            // step kt+1 and the copies of step kt+NS (into `cur`, now free)
-            read_a(0, nxt, 0, 0);
-            read_b(0, nxt, 0);
-            mfmas(1, 1, 1);
-            round16();
-            if constexpr (WC) copy_step(kt + NS, cur);
-            sched_slice<NM, NRB, 0x020, WC ? NL : 0, false>();
-        }
-        };
-        if constexpr (NPW > 0) run_loop(std::false_type{});
-        else if (copy_wave) run_loop(std::true_type{});
-        else run_loop(std::false_type{});
-
-        __builtin_amdgcn_s_waitcnt(0);
-        if (seg == 1 && p.sub) negate_acc();
     }
     if constexpr (FOLD) {
 #pragma unroll
