@@ -105,9 +105,12 @@ gba_status gemm_bias_act(gba_layout layoutA, gba_layout layoutB,
  * the fastest per problem size (Experimental Evaluation section); this entry
  * point exposes that choice for sweeps.  tile_id indexes the table reported
  * by gba_tile_info; tile_id < 0 means "let the library choose" (identical to
- * gemm_bias_act).  A tile larger than the problem (bm > M or bn > N) is
- * replaced by the library's choice, and operands that miss the fast path's
- * alignment conditions use the general kernel whatever tile_id says.  Errors
+ * gemm_bias_act).  The id that gba_select_tile answers runs the kernel the
+ * library would run on that tile (a variant of it with more LDS stages and
+ * waves that only copy, where that is the choice).  A tile larger than the
+ * problem (bm > M or bn > N) is replaced by the library's choice, and operands
+ * that miss the fast path's alignment conditions use the kernels for those
+ * whatever tile_id says.  Errors
  * as gemm_bias_act, plus GBA_EINVAL for a tile_id at or beyond
  * gba_num_tiles().
  */
@@ -271,7 +274,8 @@ gba_status gba_fused_plan(const gba_fused_desc *desc, gba_plan *plan);
  * Fast path: 16-byte aligned A, B, C and (if used) P, Q, bias; lda, ldb,
  * ldc (and ldp, ldq, ldbias when used) multiples of 8 and below 2^21 for
  * the operands; N and the contiguous extents of all operands multiples of 8.
- * Anything else takes the general kernel.  Outputs must not alias inputs.
+ * Anything else takes the kernels for such requests, which need
+ * 2-byte alignment only.  Outputs must not alias inputs.
  *
  * Degenerate sizes: M == 0 or N == 0 -> GBA_OK, nothing launched; K == 0
  * or K2 == 0 make that product's empty sum zero.
@@ -331,7 +335,9 @@ gba_status gba_tile_info(int tile_id, int *bm, int *bn, int *bk, int *waves, int
  * problem on its aligned fast path (host-only computation, no GPU access).
  * gba_fused_gemm makes the same choice for requests without the prologue
  * (K being the total reduction length of both products); with the prologue
- * it may take another tile.  Returns the tile id, or -1 if the arguments
+ * it may take another tile, and requests of few rows or few outputs over a
+ * long reduction may run on the few-row kernel instead (see gba_fused_plan).
+ * Returns the tile id, or -1 if the arguments
  * are invalid or the problem is smaller than every tile (M < 32 or N < 32:
  * general path).
  */

@@ -689,9 +689,17 @@ Plan make_plan(const gba_fused_desc &d, bool may_split)
     if (may_split && d.split_k == 0 && !tile_ok && fp32) auto_s = auto_splits(d.M, d.N, ktot);
     const bool pro = d.prologue == GBA_PRO_RELU;
     const bool asked_split = may_split && d.split_k >= 2 && fp32;
-    if (tile_ok) pl.tile = d.tile_id;
-    else if (auto_s > 1) pl.tile = auto_split_tile(d);
-    else {
+    if (tile_ok) {
+        // The id that the queries answer for a request runs the kernel the
+        // library runs it on, its deep variant included.
+        pl.tile = d.tile_id;
+        if (!asked_split) {
+            const int deep = deep_choice(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB);
+            if (deep >= 0 && deep_tile(d.layoutA, d.layoutB, deep) == d.tile_id) pl.deep = deep;
+        }
+    } else if (auto_s > 1) {
+        pl.tile = auto_split_tile(d);
+    } else {
         // A requested split is kept where the rule's tile can make it (a
         // k-group tile, a deep variant and the few-row kernel cannot).
         pl.tile = asked_split ? select_tile(d.M, d.N, ktot, d.accum, d.layoutA, d.layoutB, pro) : -1;

@@ -2,6 +2,7 @@
 gba_fused_plan (no GPU).  The measured choices name their times (MI355X,
 microseconds, operands in cache)."""
 import ctypes
+import random
 
 import pytest
 
@@ -192,3 +193,23 @@ def test_unaligned_fp16(layout, M, N, K, want):
 ])
 def test_unaligned_256x256_tile(layout, M, N, K, want):
     assert plan(M, N, K, layout, pad=1)["bm"] == want
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("prologue", [False, True])
+def test_forcing_the_answered_tile_changes_nothing(layout, prologue):
+    """bench.py's mlp_down workload (8192 x 1024 x 4096) forced the id it was
+    told and ran the plain 256x128 tile in place of its deep variant."""
+    rng, deep = random.Random(5), 0
+    shapes = [(8192, 1024, 4096), (2048, 2048, 2048), (1024, 1920, 1280)] + [
+        tuple(8 * rng.randint(4, 512) for _ in range(3)) for _ in range(400)]
+    for M, N, K in shapes:
+        want = plan(M, N, K, layout, prologue=prologue)
+        if want["path"] not in ("tile", "deep"):
+            continue
+        deep += want["path"] == "deep"
+        t = gba.fused_tile(desc(M, N, K, layout, prologue=prologue))
+        assert plan(M, N, K, layout, prologue=prologue, tile=t) == want, (M, N, K)
+    assert deep >= 10
+    p = plan(2048, 2048, 2048, layout, tile=4, split=2, workspace=1 << 30)
+    assert p["path"] == "tile" and p["splits"] == 2  # a split is kept
