@@ -1,9 +1,12 @@
 """Helpers shared by the GPU tests: device copies of stored operands and the
 element-wise parity check against the oracle."""
+import contextlib
+
 import numpy as np
 
 from oracle import oracle as O
 from paper_2006_12645_amd import datagen as D
+from paper_2006_12645_amd import gba
 
 # |gpu - oracle| <= ATOL + RTOL * |oracle|: fp32 accumulation uses the bound
 # the method is held to; fp16 accumulation (running sum rounded to fp16 every
@@ -22,6 +25,30 @@ def device_operand(logical, layout, pad=0):
     if layout == D.ROW:
         return t[:, :cols]
     return t[:, :rows].t()
+
+
+def misaligned(x):
+    """A contiguous CUDA copy of a numpy vector or matrix at a 2-byte aligned
+    address that is no multiple of 4."""
+    import torch
+    t = torch.empty(x.size + 1, dtype=torch.float16, device="cuda")[1:].view(x.shape)
+    t.copy_(torch.from_numpy(x))
+    assert t.data_ptr() % 4 == 2
+    return t
+
+
+@contextlib.contextmanager
+def recorded_plans(monkeypatch):
+    """The plans (gba.fused_plan) of the fused_gemm calls made inside."""
+    plans, launch = [], gba.fused_gemm_desc
+
+    def record(desc, *args):
+        plans.append(gba.fused_plan(desc))
+        launch(desc, *args)
+
+    with monkeypatch.context() as m:
+        m.setattr(gba, "fused_gemm_desc", record)
+        yield plans
 
 
 def oracle_for(A, B, bias, act=O.ACT_RELU, rows=None):

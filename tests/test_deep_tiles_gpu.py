@@ -15,7 +15,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def check(M, N, K, layout, K2, prologue, tile):
+def check(monkeypatch, M, N, K, layout, K2, prologue, tile):
     print("CASE", M, N, K, layout, K2, prologue, flush=True)
     la, lb = D.LAYOUT_NAMES[layout]
     assert gba.select_tile(M, N, K + K2, la, lb) in tile, "not the tile this case is about"
@@ -25,9 +25,11 @@ def check(M, N, K, layout, K2, prologue, tile):
         P, Q, _ = D.random_problem(72000 + M + K, M, N, K2)
         kw.update(P=U.device_operand(P, la, 8), Q=U.device_operand(Q, lb, 8), second="sub")
         okw.update(second=-1, p_store=D.store(P, D.ROW), q_store=D.store(Q, D.COL), K2=K2)
-    out = gba.fused_gemm(U.device_operand(A, la, 8), U.device_operand(B, lb, 8), bias=torch.from_numpy(bias).cuda(),
-                         act="relu", prologue="relu" if prologue else None, **kw)
+    with U.recorded_plans(monkeypatch) as plans:
+        out = gba.fused_gemm(U.device_operand(A, la, 8), U.device_operand(B, lb, 8), bias=torch.from_numpy(bias).cuda(),
+                             act="relu", prologue="relu" if prologue else None, **kw)
     torch.cuda.synchronize()
+    assert plans[0]["path"] == "deep", plans
     rows = np.unique(np.concatenate([np.arange(40), np.arange(M - 300, M)]))
     ref = O.fused(D.store(A, D.ROW), D.ROW, D.store(B, D.COL), D.COL, M, N, K, bias=bias, act=O.ACT_RELU,
                   prologue_relu=prologue, rows=rows, **okw)
@@ -40,19 +42,19 @@ PRODUCTS = [(False, False), (True, False), (False, True), (True, True)]  # prolo
 @pytest.mark.parametrize("prologue,second", PRODUCTS)
 @pytest.mark.parametrize("layout", ["RR", "RC", "CC"])
 @pytest.mark.parametrize("M,N,K", [(1000, 1400, 392), (2000, 960, 712)])
-def test_half(M, N, K, layout, prologue, second):
-    check(M, N, K - 72 if second else K, layout, 72 if second else 0, prologue, (5, 7))
+def test_half(monkeypatch, M, N, K, layout, prologue, second):
+    check(monkeypatch, M, N, K - 72 if second else K, layout, 72 if second else 0, prologue, (5, 7))
 
 
 @pytest.mark.parametrize("prologue,second", PRODUCTS)
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 @pytest.mark.parametrize("M,N,K", [(1992, 1800, 400), (2048, 2040, 968)])
-def test_square(M, N, K, layout, prologue, second):
-    check(M, N, K - 136 if second else K, layout, 136 if second else 0, prologue, (4,))
+def test_square(monkeypatch, M, N, K, layout, prologue, second):
+    check(monkeypatch, M, N, K - 136 if second else K, layout, 136 if second else 0, prologue, (4,))
 
 
 @pytest.mark.parametrize("prologue,second", PRODUCTS)
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 @pytest.mark.parametrize("M,N,K", [(4000, 1920, 2056)])
-def test_wide(M, N, K, layout, prologue, second):
-    check(M, N, K - 520 if second else K, layout, 520 if second else 0, prologue, (2, 3))
+def test_wide(monkeypatch, M, N, K, layout, prologue, second):
+    check(monkeypatch, M, N, K - 520 if second else K, layout, 520 if second else 0, prologue, (2, 3))

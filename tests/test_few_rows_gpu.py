@@ -17,7 +17,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def check(M, N, K, layout, K2=0, second="sub", prologue=None, bias="full", bias_op="sub", act="none", pad=1, seed=0):
+def check(monkeypatch, M, N, K, layout, K2=0, second="sub", prologue=None, bias="full", bias_op="sub", act="none", pad=1,
+          seed=0, blocks=None, rows=None):
     print("CASE", M, N, K, layout, K2, second, prologue, bias, act, pad, flush=True)
     A, B, row = D.random_problem(61000 + seed, M, N, K)
     b = {"row": row, "full": D.uniform_f16(62000 + seed, (M, N)), None: None}[bias]
@@ -28,15 +29,21 @@ def check(M, N, K, layout, K2=0, second="sub", prologue=None, bias="full", bias_
         kw.update(P=U.device_operand(P, la, pad), Q=U.device_operand(Q, lb, pad), second=second)
         okw.update(second=1 if second == "add" else -1, p_store=D.store(P, D.ROW), q_store=D.store(Q, D.COL), K2=K2)
     if b is not None:
-        kw.update(bias=torch.from_numpy(b).cuda(), bias_op=bias_op)
+        kw.update(bias=U.misaligned(b) if pad % 2 else torch.from_numpy(b).cuda(), bias_op=bias_op)
         okw.update(bias=b, bias_kind=O.BIAS_ROW if b.ndim == 1 else O.BIAS_FULL, bias_sign=1 if bias_op == "add" else -1)
     else:
         okw.update(bias=None, bias_kind=O.BIAS_NONE)
     around = torch.full((M + 2, N + 3), 7.0, dtype=torch.float16, device="cuda")
     out = around[1:M + 1, 1:N + 1]
-    gba.fused_gemm(U.device_operand(A, la, pad), U.device_operand(B, lb, pad), prologue=prologue, act=act, out=out, **kw)
+    with U.recorded_plans(monkeypatch) as plans:
+        gba.fused_gemm(U.device_operand(A, la, pad), U.device_operand(B, lb, pad), prologue=prologue, act=act, out=out,
+                       **kw)
     torch.cuda.synchronize()
+    assert plans[0]["path"] == "few_rows" and blocks in (None, (plans[0]["bm"], plans[0]["bn"])), plans
     got = out.cpu().numpy()
+    if rows is not None:
+        got = got[rows]
+        okw.update(rows=rows)
     ref = O.fused(D.store(A, D.ROW), D.ROW, D.store(B, D.COL), D.COL, M, N, K, prologue_relu=prologue == "relu",
                   act={"none": O.ACT_NONE, "relu": O.ACT_RELU, "tanh": O.ACT_TANH}[act], **okw)
     U.assert_close(got, ref, what=f"{M}x{N}x{K} {layout}")
@@ -47,34 +54,60 @@ def check(M, N, K, layout, K2=0, second="sub", prologue=None, bias="full", bias_
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 @pytest.mark.parametrize("M,N,K,K2", [
     (1, 64, 64, 0), (1, 65, 1, 0), (16, 33, 63, 65), (17, 96, 65, 0), (31, 130, 129, 7),
-    (5, 48, 300, 520), (3, 1000, 515, 0), (16, 47, 1100, 0), (24, 4112, 200, 0),
-    (7, 16473, 600, 0), (20, 16473, 300, 0),  # more columns than one round of any blocks covers
+    (5, 48, 300, 520), (3, 1000, 515, 0), (16, 47, 1100, 0), (24, 4112, 600, 0),
+    (7, 16473, 1100, 0), (20, 16473, 2100, 0),  # more columns than one round of any blocks covers
 ])
-def test_fewer_rows_than_any_tile(M, N, K, K2, layout):
-    check(M, N, K, layout, K2, prologue="relu" if K2 else None, seed=M + N + K)
+def test_fewer_rows_than_any_tile(monkeypatch, M, N, K, K2, layout):
+    check(monkeypatch, M, N, K, layout, K2, prologue="relu" if K2 else None, seed=M + N + K)
 
 
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 @pytest.mark.parametrize("M,N,K,K2", [
     (32, 264, 4096, 0),     # 16 waves, whole slabs
     (256, 256, 1544, 0),    # the last of one round of 16x16 workgroups (column-major B)
-    (40, 2048, 1600, 264),  # 16x32 / 16x64 blocks, both products
-    (64, 4096, 1536, 0),    # 32x64 blocks (row-major B)
+    (40, 2048, 2100, 264),  # 16x32 blocks, both products
 ])
-def test_taken_from_the_tiles(M, N, K, K2, layout):
-    check(M, N, K, layout, K2, second="add", prologue="relu" if K2 else None, bias="row", bias_op="add", act="relu",
-          pad=8, seed=K)
+def test_taken_from_the_tiles(monkeypatch, M, N, K, K2, layout):
+    check(monkeypatch, M, N, K, layout, K2, second="add", prologue="relu" if K2 else None, bias="row", bias_op="add",
+          act="relu", pad=8, seed=K)
+
+
+@pytest.mark.parametrize("layout", ["RR", "CR"])
+@pytest.mark.parametrize("M,N,blocks", [(64, 4096, (16, 64)), (72, 5416, (32, 64))])
+def test_larger_blocks_of_row_major_b(monkeypatch, M, N, blocks, layout):
+    check(monkeypatch, M, N, 3080, layout, bias="row", bias_op="add", act="relu", pad=8, seed=M, blocks=blocks,
+          rows=np.r_[:3, 15:18, 31:34, 47:49, M - 10:M])
 
 
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
 @pytest.mark.parametrize("M,N,K,K2", [(64, 512, 16399, 0), (100, 100, 16400, 0), (65, 127, 9001, 8001)])
-def test_long_reductions_outside_the_fast_path(M, N, K, K2, layout):
-    check(M, N, K, layout, K2, prologue="relu" if K2 else None, bias="row", act="relu", seed=K)
+def test_long_reductions_outside_the_fast_path(monkeypatch, M, N, K, K2, layout):
+    check(monkeypatch, M, N, K, layout, K2, prologue="relu" if K2 else None, bias="row", act="relu", seed=K)
 
 
 @pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
-def test_empty_reduction_is_the_bias(layout):
-    check(9, 80, 0, layout, bias="row", bias_op="sub", act="tanh")
+def test_empty_reduction_is_the_bias(monkeypatch, layout):
+    check(monkeypatch, 9, 80, 0, layout, bias="row", bias_op="sub", act="tanh")
+
+
+@pytest.mark.parametrize("layout", ["RR", "RC", "CR", "CC"])
+@pytest.mark.parametrize("M,N,K,want", [(5, 75, 130, "few_rows"), (70, 75, 130, "unaligned")])
+def test_largest_leading_dimension_of_32_bit_offsets(monkeypatch, M, N, K, want, layout):
+    """Both kernels for requests outside the fast path address a tile with
+    32-bit offsets up to leading dimensions of 2^23 - 1."""
+    A, B, _ = D.random_problem(64500, M, N, K)
+    ld = (1 << 23) - 1
+
+    def far(x, row_major):
+        x = torch.from_numpy(x if row_major else np.ascontiguousarray(x.T)).cuda()
+        t = torch.empty(x.shape[0] * ld, dtype=torch.float16, device="cuda").view(x.shape[0], ld)[:, :x.shape[1]]
+        t.copy_(x)
+        return t if row_major else t.t()
+
+    with U.recorded_plans(monkeypatch) as plans:
+        got = gba.fused_gemm(far(A, layout[0] == "R"), far(B, layout[1] == "R"), act="none")
+    assert plans[0]["path"] == want, plans
+    U.assert_close(got.cpu().numpy(), U.oracle_for(A, B, None, act=O.ACT_NONE), what=layout)
 
 
 def test_infinite_operand_reaches_only_its_outputs():

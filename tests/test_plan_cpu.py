@@ -213,3 +213,12 @@ def test_forcing_the_answered_tile_changes_nothing(layout, prologue):
     assert deep >= 10
     p = plan(2048, 2048, 2048, layout, tile=4, split=2, workspace=1 << 30)
     assert p["path"] == "tile" and p["splits"] == 2  # a split is kept
+
+
+def test_leading_dimensions_beyond_32_bit_offsets_take_the_general_kernel():
+    for M, want in ((5, "few_rows"), (70, "unaligned")):
+        for layout in LAYOUTS:
+            for over in (0, 1):
+                d = desc(M, 75, 130, layout)
+                d.lda = d.ldb = (1 << 23) - 1 + over
+                assert gba.fused_plan(d)["path"] == ("general" if over else want)
