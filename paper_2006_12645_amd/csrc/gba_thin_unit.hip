@@ -5,22 +5,12 @@
 namespace gba {
 namespace {
 
-template <int LA, int LB, int TN>
-LaunchFn pick(int tm)
-{
-    return tm == 1 ? &launch_thin<LA, LB, 1, TN> : &launch_thin<LA, LB, 2, TN>;
-}
-
 template <int LA, int LB>
 LaunchFn pick(int tm, int tn)
 {
-    if constexpr (LB == COL) {
-        if (tn == 1) return pick<LA, LB, 1>(tm);
-        return pick<LA, LB, 2>(tm);
-    } else {
-        if (tn == 2) return pick<LA, LB, 2>(tm);
-        return pick<LA, LB, 4>(tm);
-    }
+    constexpr int T = LB == COL ? 1 : 2;   // the smallest blocks' columns, in 16s
+    if (tm == 2) return &launch_thin<LA, LB, 2, 2 * T>;
+    return tn == T ? &launch_thin<LA, LB, 1, T> : &launch_thin<LA, LB, 1, 2 * T>;
 }
 
 }  // namespace

@@ -207,9 +207,9 @@ hipError_t launch_generic(const GemmArgs &a, hipStream_t s)
 }
 
 // The few-row kernel, for one layout pair (the prologue and the second
-// product are run-time options there): thin_launcher(LA, LB, TM, TN), TM in
-// {1, 2} row blocks of 16 and TN column blocks of 16 (1 or 2 with
-// column-major B, 2 or 4 with row-major B).
+// product are run-time options there): thin_launcher(LA, LB, TM, TN), TM row
+// blocks of 16 by TN column blocks of 16: 1x1, 1x2 or 2x2 with column-major
+// B, 1x2, 1x4 or 2x4 with row-major B.
 template <int LA, int LB, int TM, int TN>
 hipError_t launch_thin(const GemmArgs &a, hipStream_t s)
 {
