@@ -110,6 +110,17 @@ def test_largest_leading_dimension_of_32_bit_offsets(monkeypatch, M, N, K, want,
     U.assert_close(got.cpu().numpy(), U.oracle_for(A, B, None, act=O.ACT_NONE), what=layout)
 
 
+def test_very_many_columns():
+    """One row by 2.8e8 columns: as a launch of the few-row kernel 2^32 threads
+    and more, which the runtime refuses."""
+    N, K = 280_000_000, 8
+    column = ((torch.arange(N, dtype=torch.int32, device="cuda") % 251 - 125).half() / 128)
+    B = torch.empty((N, K), dtype=torch.float16, device="cuda")
+    B.copy_(column[:, None])
+    out = gba.gemm_bias_act(torch.full((1, K), 0.5, dtype=torch.float16, device="cuda"), B.t(), act="none")
+    assert torch.equal(out[0], column * 4)
+
+
 def test_infinite_operand_reaches_only_its_outputs():
     """Padding and clamped reads never mix: an infinity in one row of A or
     in B's storage past K changes no other output."""

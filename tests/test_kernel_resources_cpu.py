@@ -1,5 +1,5 @@
-"""Register budget of the 16x16x32 kernels, read from the device compiler's
-resource report (no GPU needed).
+"""Register budget of the kernels, read from the device compiler's resource
+report (no GPU needed).
 
 An 8-wave tile of at most 128x128 outputs is sized to run two workgroups per
 compute unit: each wave then has at most 128 VGPRs.  A change that pushes
@@ -34,12 +34,12 @@ pytestmark = pytest.mark.skipif(not _have_hipcc(), reason="hipcc not available")
 NAME = re.compile(r"Function Name: (\S+)")
 FIELD = re.compile(r"remark:\s+(VGPRs|ScratchSize \[bytes/lane\]|Occupancy \[waves/SIMD\]): (\d+)")
 SPILL = re.compile(r"remark:\s+VGPRs Spill: (\d+)")
-ARGS = re.compile(r"gemm_bias_act_fast16(I.*)EvNS_8GemmArgsE")
+ARGS = r"gemm_bias_act_%s(I.*)EvNS_8GemmArgsE"
 
 
-def template_args(mangled):
+def template_args(mangled, kernel="fast16"):
     """Integer and bool template arguments of a mangled kernel name, in order."""
-    m = ARGS.search(mangled)
+    m = re.search(ARGS % kernel, mangled)
     return [int(v) for v in re.findall(r"L[ib](-?\d+)E", m.group(1))] if m else None
 
 
@@ -65,19 +65,23 @@ def resources(unit, tmp):
     return out
 
 
-@pytest.fixture(scope="module")
-def fast16_kernels():
-    units = [u for u in B.UNITS if u[0] == "gba_gemm_unit.hip"]
+def kernels_of(source, kernel):
+    units = [u for u in B.UNITS if u[0] == source]
     with tempfile.TemporaryDirectory() as tmp, cf.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
         reports = list(ex.map(lambda u: resources(u, tmp), units))
     kernels = {}
     for rep in reports:
         for name, res in rep.items():
-            args = template_args(name)
+            args = template_args(name, kernel)
             if args is not None:
                 kernels[name] = (args, res)
-    assert kernels, "no 16x16x32 kernel found in the resource report"
+    assert kernels, f"no {kernel} kernel found in the resource report"
     return kernels
+
+
+@pytest.fixture(scope="module")
+def fast16_kernels():
+    return kernels_of("gba_gemm_unit.hip", "fast16")
 
 
 def test_small_eight_wave_tiles_fit_two_workgroups_per_cu(fast16_kernels):
@@ -124,3 +128,25 @@ def test_256x256_tile_spills_no_more_than_measured(fast16_kernels):
             seen += 1
             assert res["Spill"] <= SPILLS_256.get(tuple(args[6:11]), 0), (args, res)
     assert seen == 32, seen
+
+
+def test_few_row_kernels_do_not_spill():
+    """<A layout, B layout, row blocks, column blocks>: 16 waves of a workgroup
+    have 128 registers each (up to three blocks), 8 have 256."""
+    kernels = kernels_of("gba_thin_unit.hip", "thin")
+    assert len(kernels) == 4 * 3
+    for args, res in kernels.values():
+        assert res["Spill"] == 0 and res["ScratchSize"] == 0, (args, res)
+        assert res["Occupancy"] >= (4 if args[2] + args[3] <= 3 else 2), (args, res)
+
+
+def test_unaligned_kernels_spill_no_more_than_measured():
+    """<BM, BN, WM, WN, A layout, B layout, fp16 accumulation>: the 128x128
+    tile runs two workgroups per compute unit.  The 256x256 one (fp32 only)
+    spills, in RC outside its loop."""
+    spills = {(256, 0, 0, 0): 7, (256, 0, 1, 0): 36, (256, 1, 1, 0): 38, (128, 0, 1, 1): 3}
+    kernels = kernels_of("gba_ragged_unit.hip", "ragged")
+    assert len(kernels) == 4 * 5
+    for args, res in kernels.values():
+        assert res["Spill"] <= spills.get((args[0], *args[4:]), 0), (args, res)
+        assert res["Occupancy"] >= (4 if args[0] == 128 else 2), (args, res)
