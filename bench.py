@@ -75,7 +75,7 @@ def kernel_source_digest():
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2006_12645_amd", "csrc")
     for name in sorted(os.listdir(csrc)):
-        if name.endswith((".hip", ".hpp")):
+        if name.endswith((".hip", ".hpp", ".inc")):
             h.update(name.encode())
             h.update(strip_comments(open(os.path.join(csrc, name), encoding="utf-8").read()).encode())
     return h.hexdigest()

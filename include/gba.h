@@ -205,7 +205,8 @@ gba_status gba_fused_workspace_size(const gba_fused_desc *desc, size_t *bytes);
  * gba_fused_tile -- the tile configuration gba_fused_gemm would run the
  * request on, given the workspace the descriptor carries (host-only
  * computation, no GPU access): *tile is the tile id (see gba_tile_info), or
- * -1 for the general path and for an empty output.  The library's choice
+ * -1 for a request that runs on none (outside the fast path, smaller than
+ * every tile, or an empty output).  The library's choice
  * depends on the shape, the layouts, the accumulation and the prologue (see
  * gba_select_tile); a requested tile_id that fits is kept.  When the library
  * chooses, a request of few rows or few outputs over a long reduction may run

@@ -36,7 +36,8 @@ struct GemmArgs {
     float bias_sign;       // +1: add the bias, -1: subtract it
     int sub;               // nonzero: C = A.B - P.Q instead of A.B + P.Q
     int tiles_m, tiles_n;
-    int pro, waves;        // few-row kernel only: nonzero for the ReLU prologue; waves per workgroup
+    int pro;               // nonzero for the ReLU prologue (kernels for which it is a run-time option: few-row, ragged)
+    int waves;             // per workgroup of the few-row kernel
     // Reduction split across workgroups (splits > 1): workgroup b computes
     // split b % splits of output tile b / splits, i.e. reduction steps
     // [split * split_steps, (split + 1) * split_steps) of the steps of A.B

@@ -2,7 +2,9 @@
 // tiles, every operand layout; and the four-stage small tiles without the
 // prologue: all of them when both operand tiles are reduction-contiguous,
 // the 32x128 one with row-major B and the 128x32 one with column-major A,
-// whose M- or N-contiguous operand tile has 128 elements per row).
+// whose M- or N-contiguous operand tile has 128 elements per row; and the
+// deep variants of the 128x64 / 64x128, 128x128 and 256x128 / 128x256 tiles,
+// three or four stages with copy-only waves).
 //
 // Same decomposition as gemm_bias_act_fast (block tile per workgroup, warp
 // tiles per wave, 64-deep reduction steps through direct global -> LDS
@@ -56,7 +58,8 @@ __device__ __forceinline__ int perm16(int t, int rho)
 
 // Waves that only issue copies, added to the workgroups of the small tiles
 // (one, two or four computing waves, latency-bound: with the copies on the
-// computing waves each 64-deep step waits for their issue).  Four of them,
+// computing waves each 64-deep step waits for their issue) and of the deep
+// variants.  Four of them,
 // with fp16 accumulation: 32 x 4096 x 1024 on the 32x32 tile 9.2 -> 6.8 us,
 // 1024 x 1024 x 4096 on the 64x64 tile 28.2 -> 21.7 us (one or two gave
 // less).  On the larger four-wave tiles (64x32 to 128x64 warp tiles, three

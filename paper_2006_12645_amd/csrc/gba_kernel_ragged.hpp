@@ -221,7 +221,10 @@ __global__ void __launch_bounds__(64 * WM * WN, BM * BN == 128 * 128 ? 4 : 2) ge
     // registers for one only: refilled right after it was written to LDS, or
     // (256x256) spread over the two slices after that, since at 2-byte
     // alignment a load takes the address unit up to three times as long as
-    // an aligned one (4095^3 RC 177 us in one slice, 139 in two).
+    // an aligned one (4095^3 RC 177 us in one slice, 139 in two, eight
+    // launches at a time; under a sustained load 163).  That tile's sums and
+    // copies need a few registers more than there are: in RC they spill
+    // outside the loop, in CC two of them in every step.
     constexpr int D = BM * BN <= 64 * 64 ? 2 : 1;
     constexpr bool LATE_B = BM * BN > 128 * 128;
     // The prologue's ReLU as a signed 16-bit max (with the smallest value

@@ -4,8 +4,8 @@
 //
 // With a few rows the product is bound by reading B once, and below that by
 // latency: the tiled kernels walk K in steps that wait for each other on
-// one compute unit per 64 columns.  Here a workgroup owns 16 * TN columns
-// and all rows, and its up to 16 waves split K between them (the Split-K
+// one compute unit per 64 columns.  Here a workgroup owns 16 * TM rows by
+// 16 * TN columns, and its up to 16 waves split K between them (the Split-K
 // subsection's partition of the reduction inside a thread block).  A wave
 // loads its operands' 64-deep slabs into registers D slabs ahead, 16 bytes
 // per lane with consecutive lanes along each row, and passes every slab

@@ -114,7 +114,8 @@ struct LayoutTable {
 // Which tiles run the 16x16x32 kernel (gemm_bias_act_fast16): the ones
 // with eight waves of one k-group, in every layout where an M- or
 // N-contiguous operand tile has 128 or more elements per row (its
-// conflict-free group permutation needs eight 16-element groups); and,
+// conflict-free group permutation needs eight 16-element groups); the deep
+// variants (deep_cfg); and,
 // without prologue, the four-stage small tiles (21-25) under the same layout condition (all
 // of them in the layout where both operand tiles are reduction-contiguous,
 // 32x128 with row-major B, 128x32 with column-major A), where the 16x16x32
