@@ -118,6 +118,35 @@ int select_tile_rest(int64_t M, int64_t N, int64_t K, int accum, int small);
 // ones.
 constexpr double RIDGE_AI = 315.0;
 
+// The most rows of A and columns of B that one XCD's workgroups read between
+// them where every XCD gets its share of tile t's (the kernels' tile_coords:
+// a contiguous range, walked in groups of four tile rows).
+int64_t xcd_rows(int t, int64_t M, int64_t N)
+{
+    const int64_t bm = TILES[t].bm, bn = TILES[t].bn, tm = ceil_div(M, bm), tn = ceil_div(N, bn);
+    const int64_t nwg = tm * tn, per = 4 * tn;
+    int64_t most = 0;
+    for (int64_t x = 0; x < 8; ++x) {
+        const int64_t first = x * (nwg / 8) + (x < nwg % 8 ? x : nwg % 8), last = first + nwg / 8 + (x < nwg % 8) - 1;
+        if (last < first) break;
+        const int64_t g0 = first / per, g1 = last / per;
+        auto rows_of = [&](int64_t g) { return tm - 4 * g < 4 ? tm - 4 * g : 4; };
+        const int64_t h0 = rows_of(g0), h1 = rows_of(g1), c0 = (first - g0 * per) / h0, c1 = (last - g1 * per) / h1;
+        auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
+        int64_t rows, cols;
+        if (g0 == g1) {
+            rows = least(h0, last - first + 1);
+            cols = c1 - c0 + 1;
+        } else {
+            rows = least(h0, (g0 + 1) * per - first) + 4 * (g1 - g0 - 1) + least(h1, last - g1 * per + 1);
+            cols = g1 > g0 + 1 ? tn : least(tn, tn - c0 + c1 + 1);
+        }
+        const int64_t sum = least(rows * bm, M) + least(cols * bn, N);
+        most = sum > most ? sum : most;
+    }
+    return most;
+}
+
 int select_tile(int64_t M, int64_t N, int64_t K, int accum, int la, int lb, bool pro)
 {
     auto tiles = [&](int t) -> int64_t {
@@ -187,18 +216,24 @@ int select_tile(int64_t M, int64_t N, int64_t K, int accum, int la, int lb, bool
             // RR and CC: the four-stage tile with its long side along the
             // operand's contiguous direction (32x128 in RR, 128x32 in CC)
             // up to one workgroup per compute unit, over longer reductions
-            // up to two, else the 8-wave tiles below.  The second workgroup
-            // pays the longer the reduction, the sooner the larger the output
-            // side it is long on: from K * K * side = 2e9 (899 requests of
-            // 257 to 512 workgroups: 0.89x the 8-wave tiles' time, 16 more
-            // than 1.05x; 190 with K = 1024 as the line).  1088 x 1792 x 3072
-            // RR 31.4 us against 37.1 on the 8-wave 64x128 tile (from HBM
-            // 34.8 / 45.3), 4032 x 320 x 4544 CC 37.7 / 49.2 (40.7 / 62.6);
-            // RR 3488 x 376 x 1352 16.5 / 14.0, 2904 x 272 x 1976 20.0 / 17.7,
-            // CC 432 x 3112 x 1216 14.9 / 13.7; 4864 x 704 x 2112 RR (912
-            // workgroups) 43.6 / 33.0.
-            const int tn = la == GBA_ROW_MAJOR ? 24 : 25;
-            const bool two_rounds = K >= 1024 && (double)K * K * (la == GBA_ROW_MAJOR ? N : M) >= 2e9;
+            // (K >= 1024) up to two, else the 8-wave tiles below.  The second
+            // workgroup beats 128x128, which takes K = 1024 over 128 to 255
+            // workgroups; 64x128 / 128x64 it beats where the operands that
+            // one XCD's workgroups of theirs read outgrow its 4 MB L2 (their
+            // two stages don't cover what then comes from beyond it): from
+            // 3.8 MB (RR) or 3.2 MB (CC, level with cold operands from there).
+            // 343 requests of 257 to 512 workgroups (K = 1024-2600): 0.92x the
+            // 8-wave tiles' time, 8 more than 1.05x (116 with K = 1024 as the
+            // line); from HBM (78 of them) 0.92x, none slower.  512 x 4096 x
+            // 1024 CC 13.4 us against 16.0 on 128x128; 256 x 8192 x 2048 CC
+            // 21.2 / 25.5 (from HBM 24.5 / 32.6) on 128x64, 1088 x 1792 x 3072
+            // RR 31.4 / 37.1 (34.8 / 45.3) on 64x128, 4032 x 320 x 4544 CC
+            // 37.7 / 49.2 (40.7 / 62.6); below the line 512 x 4096 x 1280 RR
+            // 16.6 / 13.7, 4096 x 512 x 1280 CC 14.6 / 13.3; beyond two rounds
+            // 4864 x 704 x 2112 RR (912 workgroups) 43.6 / 33.0.
+            const int tn = la == GBA_ROW_MAJOR ? 24 : 25, t8w = la == GBA_ROW_MAJOR ? 20 : 19;
+            const bool square = K <= 1024 && tiles(18) >= 128 && tiles(18) < 256;
+            const bool two_rounds = K >= 1024 && (square || xcd_rows(t8w, M, N) * K * 2 >= (la == GBA_ROW_MAJOR ? 3800000 : 3200000));
             if (tile_fits(tn, M, N) && tiles(tn) <= (two_rounds ? 512 : 256)) return tn;
             if (ai < RIDGE_AI && (M <= 256 || N <= 256) && tile_fits(8, M, N) && tiles(8) <= 256) return 8;
         } else if (la == lb) {

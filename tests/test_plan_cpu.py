@@ -162,6 +162,13 @@ def test_few_rows_against_the_tiles(layout, M, N, K, want):
     ("CC", 4032, 320, 4544, 25),   # 37.7, 49.2
     ("CC", 432, 3112, 1216, 19),   # 14.9, 13.7
     ("CC", 1400, 1032, 1656, 25),  # 20.4, 24.7
+    ("CC", 512, 4096, 1024, 25),   # 13.4, 16.0
+    ("RR", 2048, 1024, 1024, 24),  # 14.2, 17.0
+    ("CC", 256, 8192, 2048, 25),   # 21.2, 25.5
+    ("RR", 8192, 256, 2048, 24),   # 22.1, 25.3
+    ("RR", 512, 4096, 1280, 20),   # 16.6, 13.7
+    ("RR", 1024, 2048, 1152, 20),  # 15.6, 13.0
+    ("CC", 4096, 512, 1280, 19),   # 14.6, 13.3
     ("RR", 1000, 1000, 512, 24),   # one workgroup per compute unit
 ])
 def test_fp16_four_stage_tile_on_two_rounds(layout, M, N, K, want):
