@@ -596,7 +596,11 @@ constexpr int THIN_LEAST_K[2][2][2] = {{{1536, 3073}, {1536, 2561}}, {{768, 2561
 //     / 6.8, CC 48 x 2048^2 7.8 / 11.9 -> 6.1 / 8.7.  Below the limits: RC 200
 //     x 264 x 648 4.1 / 4.7 against 4.4 / 4.8, RR 656 x 624 x 1624 10.3 /
 //     11.3 (warm), CR 872 x 576 x 2424 16.4 / 19.7 (warm), 224 x 1568 x 2680
-//     16.8 / 19.9 (warm).
+//     16.8 / 19.9 (warm).  With a second product the tiles start twice, the
+//     few-row kernel once: from 1536 (CC 416 x 288 x (1856 + 512) 8.9 / 11.6,
+//     RC 672 x 192 x (1832 + 576) 7.9 / 9.7, CR 128 x 736 x (280 + 1536) 8.3 /
+//     10.2, 992 x 256 x (864 + 1288) 10.8 / 13.3; the largest blocks in CR from
+//     3073 all the same: 416 x 1120 x (1704 + 400) 19.8 / 16.0).
 //     With column-major B the tiles keep what needs 32x32 blocks (RC 128 x
 //     2048^2 6.6 / 8.5 against 7.7 / 9.5, CC 320 x 704 x 2880 13.2 / 13.1
 //     against 15.2 / 15.0).
@@ -625,6 +629,7 @@ ThinCfg thin_cfg(const gba_fused_desc &d, bool fast, bool ragged)
         if (pick > 0 && d.M <= 48) least = 1536;   // the tiles pad more
         if (rowA && colB && d.prologue == GBA_PRO_RELU) least = pick == 0 ? 768 : 1536;   // tiles without copy-only waves
         if (!rowA && !colB && pick == 0 && groups(THIN_BLOCKS[0][0]) > 128) least = 2049;
+        if (has_second(d) && (rowA || colB || pick < 2) && least > 1536) least = 1536;   // the tiles start twice
         if (ktot < least) return none;
     } else if (ragged) {
         if (pick < 0 || ktot < 768) return none;

@@ -151,6 +151,20 @@ def test_few_rows_against_the_tiles(layout, M, N, K, want):
     assert path(M, N, K, layout) == want
 
 
+@pytest.mark.parametrize("layout,M,N,K,K2,want", [
+    # the same with a second product, for which the tiles start twice
+    ("CC", 416, 288, 1856, 512, "few_rows"),  # 8.9, 11.6
+    ("RC", 672, 192, 1832, 576, "few_rows"),  # 7.9, 9.7
+    ("RR", 512, 384, 1464, 768, "few_rows"),  # 9.9, 11.7
+    ("CR", 128, 736, 280, 1536, "few_rows"),  # 8.3, 10.2
+    ("CR", 992, 256, 864, 1288, "few_rows"),  # 10.8, 13.3
+    ("CR", 416, 1120, 1704, 400, "tile"),     # 19.8, 16.0
+    ("CC", 416, 288, 704, 824, "tile"),       # below the least K
+])
+def test_few_rows_against_the_tiles_with_a_second_product(layout, M, N, K, K2, want):
+    assert path(M, N, K, layout, K2=K2) == want
+
+
 @pytest.mark.parametrize("layout,M,N,K,want", [
     # fp16 accumulation, two workgroups of the four-stage tile per compute
     # unit against the 8-wave tile (us)
